@@ -501,7 +501,11 @@ HOT void block64(St64& s, Ld64& l, const Job& J, double al, double dt, double cm
   if (INTEG == AEB_RK4) {
     const double h2 = 0.5 * dt, h6 = dt / 6.0;
 #pragma unroll
-    for (int j = 0; j < K; ++j) rk4_step<FORM>(s, J, dt, h2, h6, cmd);
+    for (int j = 0; j < K; ++j) {
+      rk4_step<FORM>(s, J, dt, h2, h6, cmd);
+      // each step's position sum at its step (see run_steady)
+      asm volatile("" : "+v"(s.x));
+    }
     return;
   }
 #pragma unroll
@@ -695,30 +699,126 @@ __device__ inline int64_t next_chunk(unsigned long long* counter, int persistent
   return claim(counter) + static_cast<int64_t>(gridDim.x) * blockDim.x;
 }
 
-// Lane state and per-lane flags of the FP64 integration.
-struct Lane64 {
-  St64 s, sv;  // state, and start state of the block where the obstacle was passed
-  Ld64 l, lv;  // lead vehicle, and its state at that block start
-  int sk, se;  // step index at that block start, and at its end
+// Lane sets of a wavefront, one bit per lane.  The flags of the integration
+// (who is active, passed the obstacle, stopped, ...) are such sets: uniform
+// values in scalar registers, combined by scalar instructions, so the block
+// loops' tests and branches are scalar.  (As per-lane flags they took vector
+// registers and some 50 instructions and half a dozen dependent branches per
+// block, about 540 cycles where one wavefront runs alone on its SIMD.)
+using lanes_t = unsigned long long;
+HOT lanes_t ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+HOT bool in(lanes_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// After a branch that lanes take differently: no instruction, but the lanes
+// join here and not in a block further on, where the compiler would take every
+// value that arrives over several edges (the lane sets, the step index) for
+// one that differs between lanes, and put it in vector registers.
+HOT void lanes_join() { __builtin_amdgcn_wave_barrier(); }
+
+// Lane state and lane sets of the FP64 integration.
+struct Wave64 {
+  St64 s;
+  Ld64 l;               // lead vehicle
   int on1, on2, stage;  // controller: first steps of its two commands (INT_MAX: none), stage
-  bool active, collided, pend, clamped, free_lane, limited;
+  double margin;        // lead vehicle: the running minimum when the lane ended
+  // still running; passed the obstacle; passed it inside a block, and stopped
+  // inside a block (both still to be replayed); friction-limited for good;
+  // never limited; can become limited
+  lanes_t active, collided, pend, stopped, clamped, free_lane, limited;
 };
+
+// Block start states, kept in LDS for the replays.  Slot 0: the start of the
+// lanes' current block, written at every block.  When a lane passes the
+// obstacle or stops inside a block its entry is copied: slot 1 keeps the
+// block it ended in, slot 2 (stationary obstacle) the block where a lane that
+// runs on passed the obstacle.  Each lane reads and writes its own entries
+// only, so no barrier is needed.  In registers these states took 16 VGPRs of
+// every lane for the whole integration; here they cost two or four LDS writes
+// per block.
+constexpr int ROLL_MAX = 256;  // largest workgroup of the integration kernels
+enum { SAV_CUR = 0, SAV_END = 1, SAV_PASS = 2 };
+template <int OBS>
+struct Saves64 {
+  static constexpr int SLOTS = OBS == AEB_OBS_STATIONARY ? 3 : 2;
+  static constexpr int NL = OBS == AEB_OBS_LEAD ? ROLL_MAX : 1;
+  double x[SLOTS][ROLL_MAX], v[SLOTS][ROLL_MAX], a[SLOTS][ROLL_MAX];
+  double xl[2][NL], vl[2][NL], gmin[2][NL];
+  int k[SLOTS][ROLL_MAX], e[SLOTS][ROLL_MAX];  // first step of the block, and its end
+};
+
+template <int OBS>
+HOT void save_start(const Wave64& L, Saves64<OBS>& S) {
+  const int t = threadIdx.x;
+  S.x[SAV_CUR][t] = L.s.x;
+  S.v[SAV_CUR][t] = L.s.v;
+  S.a[SAV_CUR][t] = L.s.a;
+  if (OBS == AEB_OBS_LEAD) {
+    S.xl[SAV_CUR][t] = L.l.xl;
+    S.vl[SAV_CUR][t] = L.l.vl;
+    S.gmin[SAV_CUR][t] = L.l.gmin;
+  }
+}
+
+template <int OBS>
+HOT void keep_start(Saves64<OBS>& S, int slot, int k, int B) {
+  const int t = threadIdx.x;
+  S.x[slot][t] = S.x[SAV_CUR][t];
+  S.v[slot][t] = S.v[SAV_CUR][t];
+  S.a[slot][t] = S.a[SAV_CUR][t];
+  if (OBS == AEB_OBS_LEAD) {
+    S.xl[slot][t] = S.xl[SAV_CUR][t];
+    S.vl[slot][t] = S.vl[SAV_CUR][t];
+    S.gmin[slot][t] = S.gmin[SAV_CUR][t];
+  }
+  S.k[slot][t] = k;
+  S.e[slot][t] = k + B;
+}
+
+// What happened to the lanes in the block of B steps from step k: passed the
+// obstacle, or stopped.  A lane that stopped does not test its end position
+// (it may have moved back since): the replay of its block tests every step.
+// With a lead vehicle a lane below zero clearance was reached before any stop
+// in the block, since after a stop the clearance only grows.
+template <int OBS>
+HOT void block_events(Wave64& L, Saves64<OBS>& S, const Job& J, int k, int B, int impact_exit) {
+  constexpr bool LEAD = OBS == AEB_OBS_LEAD;
+  lanes_t stop = ballot(L.s.v <= 0.0) & L.active;
+  lanes_t hit = 0;
+  if (OBS == AEB_OBS_STATIONARY) hit = ballot(L.s.x > J.gap) & L.active & ~stop & ~L.collided;
+  if (LEAD) {
+    hit = ballot(L.l.gmin < 0.0) & L.active;
+    stop &= ~hit;
+  }
+  // (the sets change outside the lanes' branches, so that they stay scalar)
+  L.collided |= hit;
+  L.pend |= hit;
+  L.stopped |= stop;
+  const bool ends = LEAD || impact_exit;
+  L.active &= ~(stop | (ends ? hit : 0ull));
+  if (hit | stop) {
+    if (in(hit)) keep_start<OBS>(S, ends ? SAV_END : SAV_PASS, k, B);
+    if (in(stop)) {
+      keep_start<OBS>(S, SAV_END, k, B);
+      if (LEAD) L.margin = L.l.gmin;
+    }
+    lanes_join();
+  }
+}
 
 // The lane's brake command at step kk (constant inside every block: blocks
 // end at every command switch), and the first step with any command.
 template <bool CTL>
-__device__ inline double lane_cmd(const Lane64& L, const LaneScn& c, double a_warn, int kk) {
+__device__ inline double lane_cmd(const Wave64& L, const LaneScn& c, double a_warn, int kk) {
   if (!CTL) return kk >= c.nd ? c.a_cmd : 0.0;
   return kk >= L.on2 ? c.a_cmd : (kk >= L.on1 ? a_warn : 0.0);
 }
 
 template <bool CTL>
-__device__ inline int first_cmd(const Lane64& L, const LaneScn& c) {
+__device__ inline int first_cmd(const Wave64& L, const LaneScn& c) {
   return CTL ? min(L.on1, L.on2) : c.nd;
 }
 
 // Controller block limit of a lane: its next command switch, and the last step.
-__device__ inline int ctl_lim(const Lane64& L, int k, int nmax) {
+__device__ inline int ctl_lim(const Wave64& L, int k, int nmax) {
   // the earlier of the switches still ahead (either may be unset, INT_MAX)
   int sw = INT_MAX;
   if (L.on1 > k) sw = L.on1;
@@ -726,55 +826,61 @@ __device__ inline int ctl_lim(const Lane64& L, int k, int nmax) {
   return min(sw, nmax - 1);
 }
 
+// The lanes whose speed cannot rise over the next block (nor over any later
+// block under the same command): the brake is at or above its command and
+// falls toward it, so max(a, alim) does not rise, drag only slows, and what is
+// left of the acceleration is below zero by far more than any rounding.  A
+// stop inside the block then shows at the block's end (speed still at or below
+// zero), so such a lane may stop anywhere inside a block.  kt in steps: dt/tau.
+HOT lanes_t falling(const Wave64& L, const Job& J, double cmd, double ktdt) {
+  return ballot(J.nkd <= 0.0 && ktdt >= 0.0 && ktdt <= 1.0 && cmd <= L.s.a + 1e-9 &&
+                fmax(L.s.a, J.alim) - J.c < -1e-3);
+}
+
 // wnd: the smallest nd of the wavefront's lanes (the whole block is dead time
 // for every lane when k + B <= wnd)
 template <int OBS, int B, int INTEG, bool CTL>
-HOT void run_block64(Lane64& L, const Job& J, double al, const LaneScn& c, int k, int wnd,
-                     int impact_exit, double a_warn) {
+HOT void run_block64(Wave64& L, Saves64<OBS>& S, const Job& J, double al, const LaneScn& c, int k,
+                     int wnd, int impact_exit, double a_warn, double& xmax) {
   constexpr bool LEAD = OBS == AEB_OBS_LEAD;
   const double cmd = lane_cmd<CTL>(L, c, a_warn, k);
-  const int fcmd = first_cmd<CTL>(L, c);
-  if (OBS != AEB_OBS_NONE && !L.collided) {
-    L.sv = L.s;
-    if (LEAD) L.lv = L.l;
-    L.sk = k;
-    L.se = k + B;
-  }
+  save_start<OBS>(L, S);
   if (k + B <= wnd) {
     block64<FORM_D, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
-  } else if (__all(!L.active || L.clamped)) {
+  } else if ((L.active & ~L.clamped) == 0) {
     block64<FORM_C, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
-  } else if (__all(!L.active || L.free_lane)) {
+  } else if ((L.active & ~L.free_lane) == 0) {
     block64<FORM_F, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
   } else {
     block64<FORM_G, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
-    L.clamped = L.clamped || (L.limited && k + B > fcmd && L.s.a <= J.alim);
+    L.clamped |= L.limited & ballot(k + B > first_cmd<CTL>(L, c) && L.s.a <= J.alim);
   }
-  if (OBS == AEB_OBS_STATIONARY && L.active && !L.collided && L.s.x > J.gap) {
-    L.collided = true;
-    L.pend = true;
-    if (impact_exit) L.active = false;
-  }
-  if (LEAD && L.active && L.l.gmin < 0.0) {  // the lead was reached inside the block
-    L.collided = true;
-    L.pend = true;
-    L.active = false;
-  }
+  block_events<OBS>(L, S, J, k, B, impact_exit);
+  if (INTEG == AEB_RK4) xmax = fmax(xmax, in(L.active) ? L.s.x : xmax);
+}
+
+// Whether a K-step block (no lane of the wavefront past its limit) is the
+// right one: no active lane can stop inside it (speed above thr), or those
+// that can fall throughout it and another lane is still at least a block away
+// from its stop.
+HOT bool long_block(const Wave64& L, double thr, lanes_t fall) {
+  const lanes_t low = ballot(L.s.v <= thr) & L.active;
+  if (low == 0) return true;
+  return (low & ~fall) == 0 && (ballot(L.s.v > 2.0 * thr) & L.active) != 0;
 }
 
 // Consecutive K-step blocks in one steady form (every active lane friction-
-// limited for good, or every one never limited), for as long as no lane can
-// stop or reach the block limit wl inside the next block.  A lane's block
-// start state is kept only through its block; where the obstacle is passed
-// inside a block, that state becomes the lane's replay start.  Returns the
-// step index after the last block.
+// limited for good, or every one never limited), until the block limit wl or
+// until shorter blocks are the better choice.  Returns the step index after
+// the last block.
 template <int OBS, int K, int FORM, int INTEG>
-HOT int run_steady(Lane64& L, const Job& J, double al, double dt, double cmd, int k, int wl,
-                   double thr, int impact_exit, double& xmax) {
+HOT int run_steady(Wave64& L, Saves64<OBS>& S, const Job& J, double al, double dt, double cmd,
+                   int k, int wl, double thr, lanes_t fall, int impact_exit, double& xmax) {
   constexpr bool LEAD = OBS == AEB_OBS_LEAD;
+  bool more;
   do {
-    const St64 b = L.s;
-    const Ld64 bl = L.l;
+    k = __builtin_amdgcn_readfirstlane(k);
+    save_start<OBS>(L, S);
     // in 16-step pieces whose position is pinned in a register at the end of
     // each: with no obstacle nothing inside the run reads the position, and
     // the compiler would otherwise hold every step's speed for a position
@@ -785,39 +891,40 @@ HOT int run_steady(Lane64& L, const Job& J, double al, double dt, double cmd, in
       asm volatile("" : "+v"(L.s.x));
     }
     if (K % 16 != 0) block64<FORM, K % 16, LEAD, INTEG>(L.s, L.l, J, al, dt, cmd);
-    if (INTEG == AEB_RK4 && L.active) xmax = fmax(xmax, L.s.x);
-    bool hit = false;
-    if (OBS == AEB_OBS_STATIONARY) hit = L.active && !L.collided && L.s.x > J.gap;
-    if (LEAD) hit = L.active && L.l.gmin < 0.0;  // the lead was reached inside the block
-    if (hit) {
-      L.sv = b;
-      if (LEAD) L.lv = bl;
-      L.sk = k;
-      L.se = k + K;
-      L.collided = true;
-      L.pend = true;
-      if (LEAD || impact_exit) L.active = false;
-    }
+    block_events<OBS>(L, S, J, k, K, impact_exit);
+    if (INTEG == AEB_RK4) xmax = fmax(xmax, in(L.active) ? L.s.x : xmax);
     k += K;
-  } while (k + K <= wl && __any(L.active) && !__any(L.active && L.s.v <= thr));
+    more = k + K <= wl && L.active != 0 && long_block(L, thr, fall);
+  } while (more);
   return k;
 }
 
 template <int OBS, int K, bool BATCH, int INTEG = AEB_EULER, bool CTL = false>
-__global__ __launch_bounds__(256) void k_roll_fp64(const Job* __restrict__ jobs,
+__global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ jobs,
                                                    const LeadJob* __restrict__ leads,
                                                    const uint32_t* __restrict__ perm, int64_t n,
                                                    Ctx ctx, unsigned long long* counter,
                                                    int persistent) {
   if (ctx.hdr) n = ctx.hdr->total;  // a recorded mix: its size from the device header
-  // block ladder as a lane approaches its stop: K steps, then KM, then KS,
-  // then single checked steps (a level runs while no lane can stop inside it)
+  // block ladder: K steps, then KM, then KS, then single checked steps.  A
+  // level runs while every lane that could stop inside the block (speed below
+  // the level's bound) is one whose speed can only fall, so that its stop
+  // shows at the block's end and is found by replaying that block.  K-step
+  // blocks go on past such lanes while another lane is still at least a block
+  // away from its stop (a wavefront whose lanes stop far apart stays in the
+  // long blocks); once every lane is near, KM-step blocks, so that little runs
+  // past the last stop.  (A ladder that left the long blocks at the first
+  // lane's stop ran the spread of a wavefront's stops in short blocks and
+  // checked steps: 25,000 samples 191 us against 107, 200,000 with perception
+  // 390 against 300, 1,048,576, whose wavefronts stop together, 1.00 against
+  // 0.98 ms.)
   constexpr int KS = 4;
   constexpr int KM = K > 16 ? 16 : KS;
   // with the controller, decisions every few tens of steps leave short
   // remainders: a 2-step level before the single steps
   constexpr int K2 = CTL ? 2 : KS;
   constexpr bool LEAD = OBS == AEB_OBS_LEAD;
+  __shared__ Saves64<OBS> sav;
   for (int pass = 0;; ++pass) {
     const int64_t base = next_chunk(counter, persistent, pass, n);
     if (base >= n) break;
@@ -845,28 +952,25 @@ __global__ __launch_bounds__(256) void k_roll_fp64(const Job* __restrict__ jobs,
     // the smallest block level and its stopping bound
     constexpr int KMIN = K2 < KS ? K2 : KS;
     const double thr_min = K2 < KS ? thr_2 : thr_s;
-    Lane64 L;
+    const double ktdt = INTEG == AEB_RK4 ? J.kt * c.dt : J.kt;
+    Wave64 L;
     L.on1 = L.on2 = INT_MAX;
     L.stage = 0;
     L.s = St64{0.0, J.v0, 0.0};
     L.l = Ld64{0.0, LEAD ? J.v0 : 0.0, J.gap};
-    L.sv = L.s;
-    L.lv = L.l;
-    L.sk = L.se = 0;
-    L.active = valid;
-    L.collided = L.pend = L.clamped = false;
+    L.margin = J.gap;
+    L.active = ballot(valid);
+    L.collided = L.pend = L.stopped = L.clamped = 0;
     // never limited: a >= a_cmd - (rounding) > alim, so max(a, alim) = a
-    L.free_lane = J.alim < c.a_cmd - 1e-6;
+    L.free_lane = ballot(J.alim < c.a_cmd - 1e-6);
     // limited for good once a <= alim: a never climbs above max(a, a_cmd) < alim
-    L.limited = J.alim > c.a_cmd + 1e-9;
+    L.limited = ballot(J.alim > c.a_cmd + 1e-9);
     int end = 0, steps = 0;
-    // margin: with a lead vehicle the running minimum of the clearance, taken
-    // when the lane ends (later blocks keep integrating an ended lane's state)
-    double dist = 0.0, margin = J.gap;
+    double dist = 0.0;
     // RK4's last step may move the position back (stage speeds below zero as
     // the vehicle stops): the margin then comes from the largest position,
-    // tracked over the checked steps (blocks run only while every stage
-    // speed is positive, so inside them the position rises)
+    // tracked at block ends and over checked steps (before a stop the position
+    // rises)
     double xmax = 0.0;
     float vimp = 0.0f;
     int k = 0, wl = -1;
@@ -874,20 +978,19 @@ __global__ __launch_bounds__(256) void k_roll_fp64(const Job* __restrict__ jobs,
     int ktick = 0;
     uint32_t tick = 0;
     // every lane has ended by its step nmax (the horizon test fires at k + 1 == nmax)
-    for (;;) {
+    while (L.active) {
       // the step index is the same in every lane: keep it (and the branches on it) scalar
       k = __builtin_amdgcn_readfirstlane(k);
-      if (!__any(L.active)) break;
       if (CTL) {
         if (k == ktick) {
           // decision on the state after k steps; a raised stage's command
           // starts nd steps later.  Once every active lane is at the full
           // stage no decision can change anything: decisions stop, and so do
           // the block limits at decision steps.
-          if (!__any(L.active && L.stage < 2)) {
+          if ((ballot(L.stage < 2) & L.active) == 0) {
             ktick = INT_MAX;
           } else {
-            if (L.active && L.stage < 2) {
+            if (in(L.active) && L.stage < 2) {
               const double gt = LEAD ? (J.gap + L.l.xl) - L.s.x : (J.gap + 0.0) - L.s.x;
               const double cl = LEAD ? L.s.v - L.l.vl : L.s.v - 0.0;
               // the noise is drawn only where it can change the decision,
@@ -907,6 +1010,7 @@ __global__ __launch_bounds__(256) void k_roll_fp64(const Job* __restrict__ jobs,
                 L.stage = want;
               }
             }
+            lanes_join();
             ++tick;
             // past the last step no decision can act
             const int64_t nk = static_cast<int64_t>(ktick) + ctx.ca.period;
@@ -915,37 +1019,45 @@ __global__ __launch_bounds__(256) void k_roll_fp64(const Job* __restrict__ jobs,
           wnd = wave_min(valid ? min(L.on1, L.on2) : INT_MAX);
           wl = -1;
         }
-        if (k >= wl) wl = min(ktick, wave_min(L.active ? ctl_lim(L, k, c.nmax) : INT_MAX));
+        if (k >= wl) wl = min(ktick, wave_min(in(L.active) ? ctl_lim(L, k, c.nmax) : INT_MAX));
       } else if (!varnd || k >= wl) {
-        wl = wave_lim(varnd, L.active, k, c.nd, c.nmax);
+        wl = wave_lim(varnd, in(L.active), k, c.nd, c.nmax);
       }
-      if (k + K <= wl && !__any(L.active && L.s.v <= thr_k)) {
+      // lanes that could stop inside a K-step block need speeds that fall
+      lanes_t fall = ~0ull;
+      if (ballot(L.s.v <= thr_k) & L.active)
+        fall = falling(L, J, lane_cmd<CTL>(L, c, ctx.ca.a_warn, k), ktdt);
+      if (k + K <= wl && long_block(L, thr_k, fall)) {
         // past every lane's dead time, in a form no later block changes:
         // a run of blocks without the per-block bookkeeping
         const bool past = k + K > wnd;
-        if (past && __all(!L.active || L.clamped)) {
-          k = run_steady<OBS, K, FORM_C, INTEG>(L, J, al, c.dt, 0.0, k, wl, thr_k,
+        if (past && (L.active & ~L.clamped) == 0) {
+          // (a clamped lane's speed falls whenever its acceleration without
+          // drag is below zero)
+          const lanes_t f = ballot(J.nkd <= 0.0 && J.alim - J.c < -1e-3);
+          k = run_steady<OBS, K, FORM_C, INTEG>(L, sav, J, al, c.dt, 0.0, k, wl, thr_k, f,
                                                 ctx.impact_exit, xmax);
-        } else if (past && __all(!L.active || L.free_lane)) {
+        } else if (past && (L.active & ~L.free_lane) == 0) {
           const double cmd = lane_cmd<CTL>(L, c, ctx.ca.a_warn, k);
-          k = run_steady<OBS, K, FORM_F, INTEG>(L, J, al, c.dt, cmd, k, wl, thr_k,
+          const lanes_t f = falling(L, J, cmd, ktdt);
+          k = run_steady<OBS, K, FORM_F, INTEG>(L, sav, J, al, c.dt, cmd, k, wl, thr_k, f,
                                                 ctx.impact_exit, xmax);
         } else {
-          run_block64<OBS, K, INTEG, CTL>(L, J, al, c, k, wnd, ctx.impact_exit, ctx.ca.a_warn);
-          if (INTEG == AEB_RK4 && L.active) xmax = fmax(xmax, L.s.x);
+          run_block64<OBS, K, INTEG, CTL>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+                                          ctx.ca.a_warn, xmax);
           k += K;
         }
-      } else if (KM > KS && k + KM <= wl && !__any(L.active && L.s.v <= thr_m)) {
-        run_block64<OBS, KM, INTEG, CTL>(L, J, al, c, k, wnd, ctx.impact_exit, ctx.ca.a_warn);
-        if (INTEG == AEB_RK4 && L.active) xmax = fmax(xmax, L.s.x);
+      } else if (KM > KS && k + KM <= wl && (ballot(L.s.v <= thr_m) & L.active & ~fall) == 0) {
+        run_block64<OBS, KM, INTEG, CTL>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+                                         ctx.ca.a_warn, xmax);
         k += KM;
-      } else if (k + KS <= wl && !__any(L.active && L.s.v <= thr_s)) {
-        run_block64<OBS, KS, INTEG, CTL>(L, J, al, c, k, wnd, ctx.impact_exit, ctx.ca.a_warn);
-        if (INTEG == AEB_RK4 && L.active) xmax = fmax(xmax, L.s.x);
+      } else if (k + KS <= wl && (ballot(L.s.v <= thr_s) & L.active & ~fall) == 0) {
+        run_block64<OBS, KS, INTEG, CTL>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+                                         ctx.ca.a_warn, xmax);
         k += KS;
-      } else if (K2 < KS && k + K2 <= wl && !__any(L.active && L.s.v <= thr_2)) {
-        run_block64<OBS, K2, INTEG, CTL>(L, J, al, c, k, wnd, ctx.impact_exit, ctx.ca.a_warn);
-        if (INTEG == AEB_RK4 && L.active) xmax = fmax(xmax, L.s.x);
+      } else if (K2 < KS && k + K2 <= wl && (ballot(L.s.v <= thr_2) & L.active & ~fall) == 0) {
+        run_block64<OBS, K2, INTEG, CTL>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+                                         ctx.ca.a_warn, xmax);
         k += K2;
       } else {
         // checked single steps, in a loop of their own for as long as no
@@ -954,12 +1066,11 @@ __global__ __launch_bounds__(256) void k_roll_fp64(const Job* __restrict__ jobs,
         // step or block limit is reached
         do {
           const double cmd = lane_cmd<CTL>(L, c, ctx.ca.a_warn, k);
-          if (L.active) {
+          bool clamp = false, impact = false, done = false;
+          if (in(L.active)) {
             step64<LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
             if (INTEG == AEB_RK4) xmax = fmax(xmax, L.s.x);
-            if (k >= first_cmd<CTL>(L, c))
-              L.clamped = L.clamped || (L.limited && L.s.a <= J.alim);
-            bool impact = false;
+            clamp = k >= first_cmd<CTL>(L, c) && L.s.a <= J.alim;
             if (LEAD) {
               const double gk = (J.gap + L.l.xl) - L.s.x;
               L.l.gmin = fmin(L.l.gmin, gk);
@@ -967,101 +1078,126 @@ __global__ __launch_bounds__(256) void k_roll_fp64(const Job* __restrict__ jobs,
             } else if (OBS == AEB_OBS_STATIONARY) {
               impact = L.s.x > J.gap;
             }
-            if (impact && !L.collided) {
-              L.collided = true;
+            if (impact && !in(L.collided))
               vimp = static_cast<float>(LEAD ? L.s.v - L.l.vl : L.s.v);
-            }
-            if (impact && (LEAD || ctx.impact_exit)) {
-              L.active = false;
+            if (impact && (LEAD || ctx.impact_exit))
               end = AEB_END_IMPACT;
+            else if (L.s.v <= 0.0)
+              end = AEB_END_STOP;
+            else if (k + 1 == c.nmax)
+              end = AEB_END_HORIZON;
+            done = end != 0;
+            if (done) {
               steps = k + 1;
               dist = L.s.x;
+              if (LEAD) L.margin = L.l.gmin;
             }
-            if (L.active) {
-              if (L.s.v <= 0.0) {
-                L.active = false;
-                end = AEB_END_STOP;
-                steps = k + 1;
-                dist = L.s.x;
-              } else if (k + 1 == c.nmax) {
-                L.active = false;
-                end = AEB_END_HORIZON;
-                steps = k + 1;
-                dist = L.s.x;
-              }
-            }
-            if (LEAD && !L.active) margin = L.l.gmin;
           }
+          lanes_join();
+          L.clamped |= L.limited & ballot(clamp);
+          if (OBS != AEB_OBS_NONE) L.collided |= ballot(impact);
+          L.active &= ~ballot(done);
           k += 1;
-        } while (k < wl && !(CTL && k == ktick) && __any(L.active) &&
-                 (k + KMIN > wl || __any(L.active && L.s.v <= thr_min)));
+        } while (k < wl && !(CTL && k == ktick) && L.active != 0 &&
+                 (k + KMIN > wl || (ballot(L.s.v <= thr_min) & L.active & ~fall) != 0));
       }
     }
-    // replay the block in which each pending lane passed the obstacle.  Inside
-    // that block every speed stays positive, so the position rises (and with
-    // a lead vehicle the running minimum of the clearance can only fall): a
-    // chunk of RB steps that ends inside the block holds the crossing exactly
-    // when its end state shows it.  Chunks without the crossing are skipped
-    // whole; the one holding it then runs step by step.  The generic form is
-    // the canonical step, so both reproduce the block's states bit for bit.
-    if (OBS != AEB_OBS_NONE && __any(L.pend)) {
-      St64 r = L.sv;
-      Ld64 rl = L.lv;
-      int kr = L.sk;
+    // replay the block in which each pending lane passed the obstacle, and the
+    // block in which each stopped lane stopped.  Inside the first every speed
+    // stays positive, so the position rises (and with a lead vehicle the
+    // running minimum of the clearance can only fall); inside the second the
+    // speed only falls and the position rises until the stop.  A chunk of RB
+    // steps that ends inside the block therefore holds the event exactly when
+    // its end state shows it; chunks without one are skipped whole, the one
+    // holding it runs step by step.  The generic form is the canonical step,
+    // so the replay reproduces the block's states bit for bit.
+    auto replay = [&](lanes_t who, int slot, bool to_stop) {
+      const int t = threadIdx.x;
+      bool go = in(who);
+      St64 r{0.0, 0.0, 0.0};
+      Ld64 rl{};
+      int kr = 0, se = 0;
+      if (go) {
+        r = St64{sav.x[slot][t], sav.v[slot][t], sav.a[slot][t]};
+        if (LEAD) rl = Ld64{sav.xl[SAV_END][t], sav.vl[SAV_END][t], sav.gmin[SAV_END][t]};
+        kr = sav.k[slot][t];
+        se = sav.e[slot][t];
+      }
+      // a stopped lane may also have passed the obstacle in the same block
+      bool seek = OBS != AEB_OBS_NONE && (!to_stop || !in(L.collided));
+      bool passed = false;
       constexpr int RB = 8;
       if (K > RB) {
         // the command is constant over a block
         const double cmd = lane_cmd<CTL>(L, c, ctx.ca.a_warn, kr);
-        bool skip = L.pend;
+        bool skip = go;
         for (int it = 0; it < K / RB; ++it) {
-          skip = skip && kr + RB <= L.se;
-          if (!__any(skip)) break;
+          skip = skip && kr + RB <= se;
+          if (ballot(skip) == 0) break;
           if (skip) {
-            St64 t = r;
-            Ld64 tl = rl;
-            block64<FORM_G, RB, LEAD, INTEG>(t, tl, J, al, c.dt, cmd);
-            if (LEAD ? tl.gmin < 0.0 : t.x > J.gap) {
+            St64 q = r;
+            Ld64 ql = rl;
+            block64<FORM_G, RB, LEAD, INTEG>(q, ql, J, al, c.dt, cmd);
+            const bool over = LEAD ? ql.gmin < 0.0 : seek && q.x > J.gap;
+            if (over || (to_stop && q.v <= 0.0)) {
               skip = false;
             } else {
-              r = t;
-              rl = tl;
+              r = q;
+              rl = ql;
               kr += RB;
             }
           }
         }
       }
-      // the replay is bit-identical to the block, so the crossing recurs within it
+      if (INTEG == AEB_RK4 && to_stop && go) xmax = fmax(xmax, r.x);
+      // the event recurs within the block
       for (int it = 0; it <= K; ++it) {
-        if (!__any(L.pend)) break;
-        if (L.pend) {
+        if (ballot(go) == 0) break;
+        if (go) {
           const double cmd = lane_cmd<CTL>(L, c, ctx.ca.a_warn, kr);
           step64<LEAD, INTEG>(r, rl, J, al, c.dt, cmd);
           ++kr;
-          bool impact;
+          if (INTEG == AEB_RK4 && to_stop) xmax = fmax(xmax, r.x);
+          bool impact = false;
           if (LEAD) {
             const double gk = (J.gap + rl.xl) - r.x;
             rl.gmin = fmin(rl.gmin, gk);
             impact = gk < 0.0;
-          } else {
-            impact = r.x > J.gap;
+          } else if (OBS == AEB_OBS_STATIONARY) {
+            impact = seek && r.x > J.gap;
           }
           if (impact) {
-            L.pend = false;
+            passed = true;
+            seek = false;
             vimp = static_cast<float>(LEAD ? r.v - rl.vl : r.v);
             if (LEAD || ctx.impact_exit) {
               end = AEB_END_IMPACT;
               steps = kr;
               dist = r.x;
               xmax = r.x;
-              margin = rl.gmin;
+              L.margin = rl.gmin;
+              go = false;
             }
+            if (!to_stop) go = false;
+          }
+          if (to_stop && go && r.v <= 0.0) {
+            end = AEB_END_STOP;
+            steps = kr;
+            dist = r.x;
+            go = false;
           }
         }
       }
-    }
-    if (L.pend) vimp = __builtin_nanf("");  // unreachable; makes a broken replay visible
+      lanes_join();
+      if (OBS != AEB_OBS_NONE) L.collided |= ballot(passed);
+      if (go) vimp = __builtin_nanf("");  // unreachable; makes a broken replay visible
+    };
+    if (OBS != AEB_OBS_NONE && L.pend)
+      replay(L.pend, OBS == AEB_OBS_STATIONARY && !ctx.impact_exit ? SAV_PASS : SAV_END, false);
+    if (L.stopped) replay(L.stopped, SAV_END, true);
     if (ctx.lanes) count_lanes(ctx.lanes, k, 64);
     if (valid) {
+      double margin = L.margin;
       if (!LEAD) {
         const double mg = J.gap - (INTEG == AEB_RK4 ? xmax : dist);
         margin = mg < J.gap ? mg : J.gap;
@@ -1071,8 +1207,8 @@ __global__ __launch_bounds__(256) void k_roll_fp64(const Job* __restrict__ jobs,
       o.dist[i] = dist;
       o.margin[i] = margin;
       o.steps[i] = steps;
-      o.status[i] = static_cast<uint8_t>(end | (L.collided ? AEB_COLLIDED : 0));
-      o.vimp[i] = L.collided ? vimp : 0.0f;
+      o.status[i] = static_cast<uint8_t>(end | (in(L.collided) ? AEB_COLLIDED : 0));
+      o.vimp[i] = in(L.collided) ? vimp : 0.0f;
     }
   }
 }
@@ -1087,6 +1223,14 @@ __global__ __launch_bounds__(256) void k_roll_fp64(const Job* __restrict__ jobs,
 // over both samples of every lane; each sample's steps are the canonical
 // step's, bit for bit.
 // ---------------------------------------------------------------------------
+// state and flags of one of a lane's samples
+struct Lane64x2 {
+  St64 s, sv;  // state, and start state of the block where the obstacle was passed
+  Ld64 l;
+  int sk, se;  // step index at that block start, and at its end
+  bool active, collided, pend, clamped, free_lane, limited;
+};
+
 template <int FORM, int K>
 HOT void block64x2(St64 (&s)[2], const Job (&J)[2], double dt0, double dt1, double cmd0,
                    double cmd1) {
@@ -1102,7 +1246,7 @@ HOT void block64x2(St64 (&s)[2], const Job (&J)[2], double dt0, double dt1, doub
 }
 
 template <int OBS, int B>
-HOT void run_block64x2(Lane64 (&L)[2], const Job (&J)[2], const LaneScn (&c)[2], int k, int wnd,
+HOT void run_block64x2(Lane64x2 (&L)[2], const Job (&J)[2], const LaneScn (&c)[2], int k, int wnd,
                        int impact_exit) {
   double cmd[2];
 #pragma unroll
@@ -1140,7 +1284,7 @@ HOT void run_block64x2(Lane64 (&L)[2], const Job (&J)[2], const LaneScn (&c)[2],
 
 // runs of steady blocks for both samples of every lane (see run_steady)
 template <int OBS, int K, int FORM>
-HOT int run_steady_x2(Lane64 (&L)[2], const Job (&J)[2], const LaneScn (&c)[2], double cmd0,
+HOT int run_steady_x2(Lane64x2 (&L)[2], const Job (&J)[2], const LaneScn (&c)[2], double cmd0,
                       double cmd1, int k, int wl, const double (&thr)[2], int impact_exit) {
   St64 s[2] = {L[0].s, L[1].s};
   do {
@@ -1203,7 +1347,7 @@ __global__ __launch_bounds__(256) void k_roll_fp64x2(const Job* __restrict__ job
     uint32_t g[2];
     Job J[2];
     LaneScn c[2];
-    Lane64 L[2];
+    Lane64x2 L[2];
     double thr_k[2], thr_m[2], thr_s[2], dist[2], margin[2];
     float vimp[2];
     int end[2], steps[2];
@@ -1217,12 +1361,9 @@ __global__ __launch_bounds__(256) void k_roll_fp64x2(const Job* __restrict__ job
       thr_k[q] = static_cast<double>(K) * c[q].dt * J[q].dmax;
       thr_m[q] = static_cast<double>(KM) * c[q].dt * J[q].dmax;
       thr_s[q] = static_cast<double>(KS) * c[q].dt * J[q].dmax;
-      L[q].on1 = L[q].on2 = INT_MAX;
-      L[q].stage = 0;
       L[q].s = St64{0.0, J[q].v0, 0.0};
       L[q].l = Ld64{0.0, 0.0, J[q].gap};
       L[q].sv = L[q].s;
-      L[q].lv = L[q].l;
       L[q].sk = L[q].se = 0;
       L[q].active = valid[q];
       L[q].collided = L[q].pend = L[q].clamped = false;
