@@ -961,10 +961,14 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
     L.margin = J.gap;
     L.active = ballot(valid);
     L.collided = L.pend = L.stopped = L.clamped = 0;
-    // never limited: a >= a_cmd - (rounding) > alim, so max(a, alim) = a
-    L.free_lane = ballot(J.alim < c.a_cmd - 1e-6);
-    // limited for good once a <= alim: a never climbs above max(a, a_cmd) < alim
-    L.limited = ballot(J.alim > c.a_cmd + 1e-9);
+    // never limited: a >= a_cmd - (rounding) > alim, so max(a, alim) = a; and
+    // limited for good once a <= alim: a never climbs above max(a, a_cmd) <
+    // alim.  Both need an actuator that approaches its command from one side,
+    // RK4's stages included: a step of at most one time constant (beyond it
+    // the lane keeps the generic form).
+    const bool smooth = ktdt >= 0.0 && ktdt <= 1.0;
+    L.free_lane = ballot(smooth && J.alim < c.a_cmd - 1e-6);
+    L.limited = ballot(smooth && J.alim > c.a_cmd + 1e-9);
     int end = 0, steps = 0;
     double dist = 0.0;
     // RK4's last step may move the position back (stage speeds below zero as

@@ -55,6 +55,15 @@ def test_scattered_stops_fp64(B, orc, name, n):
     check_fp64(to_np(plain(B, d)), orc.run(d), exact=True)
 
 
+@pytest.mark.parametrize("seed", range(4))
+def test_stiff_rk4_forms(B, orc, seed):
+    """Steps of up to 2.5 actuator time constants: an RK4 stage may leave the
+    range between the brake and its command, so neither the never-limited nor
+    the limited-for-good form holds, whatever lanes share a wavefront."""
+    d = W.single(1031, seed=seed, **VARIANTS["rk4_stiff"])
+    check_fp64(to_np(plain(B, d)), orc.run(d), exact=True)
+
+
 def test_stop_and_crossing_in_one_block(B, orc):
     """Obstacles placed at the samples' own stopping distances, so that a lane
     passes the obstacle in the block it stops in, or just fails to."""
