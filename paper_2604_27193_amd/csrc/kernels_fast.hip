@@ -44,8 +44,8 @@ namespace {
 // scratch memory (the compiler declined to inline the largest forms).
 #define HOT __device__ __attribute__((always_inline)) inline
 
-// sort keys: 64 coarse length bins x 2 classes x 64 fine levels; with the
-// controller 64 decision ticks x 2 classes x 128 length levels (the sort's
+// sort keys: 2 classes x 4,096 length levels (with perception 64 coarse length
+// bins x 64 levels of length and command step); with the controller 64 decision ticks x 2 classes x 128 length levels (the sort's
 // kernels take the key count as a template argument: their per-bin loops
 // cost latency on small launches)
 constexpr int NBINS = 8192;
@@ -245,7 +245,7 @@ HOT uint32_t prep_sample(const PrepArgs& a, int64_t i, uint32_t j, int64_t local
   // other (each distinct switch step cuts the wavefront's blocks)
   const uint32_t fine =
       a.nds ? (((ud >> 3) & 7u) << 3) | ((static_cast<uint32_t>(ndl) >> 4) & 7u) : ud & 63u;
-  uint32_t key = ((ud >> 6) << 7) | (limited ? 0u : 64u) | fine;
+  uint32_t key = (limited ? 0u : 4096u) | (ud & ~63u) | fine;
   // with the controller: first the tick of the predicted full-braking
   // decision (modulo 64, latest first), so a wavefront's lanes reach the
   // thresholds, where the noise can decide and the whole wavefront draws
@@ -838,8 +838,10 @@ HOT lanes_t falling(const Wave64& L, const Job& J, double cmd, double ktdt) {
 }
 
 // wnd: the smallest nd of the wavefront's lanes (the whole block is dead time
-// for every lane when k + B <= wnd)
-template <int OBS, int B, int INTEG, bool CTL>
+// for every lane when k + B <= wnd).  TOP: a block of the top level, where the
+// steady forms are the runs' business and only the dead time and the generic
+// form are left.
+template <int OBS, int B, int INTEG, bool CTL, bool TOP>
 HOT void run_block64(Wave64& L, Saves64<OBS>& S, const Job& J, double al, const LaneScn& c, int k,
                      int wnd, int impact_exit, double a_warn, double& xmax) {
   constexpr bool LEAD = OBS == AEB_OBS_LEAD;
@@ -847,9 +849,9 @@ HOT void run_block64(Wave64& L, Saves64<OBS>& S, const Job& J, double al, const 
   save_start<OBS>(L, S);
   if (k + B <= wnd) {
     block64<FORM_D, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
-  } else if ((L.active & ~L.clamped) == 0) {
+  } else if (!TOP && (L.active & ~L.clamped) == 0) {
     block64<FORM_C, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
-  } else if ((L.active & ~L.free_lane) == 0) {
+  } else if (!TOP && (L.active & ~L.free_lane) == 0) {
     block64<FORM_F, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
   } else {
     block64<FORM_G, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
@@ -1046,21 +1048,27 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
           const lanes_t f = falling(L, J, cmd, ktdt);
           k = run_steady<OBS, K, FORM_F, INTEG>(L, sav, J, al, c.dt, cmd, k, wl, thr_k, f,
                                                 ctx.impact_exit, xmax);
+        } else if (past && (L.active & ~(L.clamped | L.free_lane)) == 0) {
+          // both kinds: the generic form, whose step serves either
+          const double cmd = lane_cmd<CTL>(L, c, ctx.ca.a_warn, k);
+          const lanes_t f = falling(L, J, cmd, ktdt);
+          k = run_steady<OBS, K, FORM_G, INTEG>(L, sav, J, al, c.dt, cmd, k, wl, thr_k, f,
+                                                ctx.impact_exit, xmax);
         } else {
-          run_block64<OBS, K, INTEG, CTL>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+          run_block64<OBS, K, INTEG, CTL, true>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
                                           ctx.ca.a_warn, xmax);
           k += K;
         }
       } else if (KM > KS && k + KM <= wl && (ballot(L.s.v <= thr_m) & L.active & ~fall) == 0) {
-        run_block64<OBS, KM, INTEG, CTL>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+        run_block64<OBS, KM, INTEG, CTL, false>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
                                          ctx.ca.a_warn, xmax);
         k += KM;
       } else if (k + KS <= wl && (ballot(L.s.v <= thr_s) & L.active & ~fall) == 0) {
-        run_block64<OBS, KS, INTEG, CTL>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+        run_block64<OBS, KS, INTEG, CTL, false>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
                                          ctx.ca.a_warn, xmax);
         k += KS;
       } else if (K2 < KS && k + K2 <= wl && (ballot(L.s.v <= thr_2) & L.active & ~fall) == 0) {
-        run_block64<OBS, K2, INTEG, CTL>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+        run_block64<OBS, K2, INTEG, CTL, false>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
                                          ctx.ca.a_warn, xmax);
         k += K2;
       } else {
@@ -1528,6 +1536,11 @@ struct L32 {
   float dt, nkd, nkt, alc, tb, td, tdm, ejump, thr, gapf;
 };
 
+// A lane whose speed is not split holds it whole in vi, with vb = 0: the sum
+// vb + vi is then vi itself and the step's update of vi the plain one, so the
+// split step serves both kinds of lanes in one wavefront (running each form
+// under its lane mask made the one wavefront that holds both the longest of
+// small launches: 25,000 samples 166 us); only the flush tells them apart.
 struct St32 {
   float vb, vi, e, p;
   Kahan32 X;
@@ -1535,7 +1548,7 @@ struct St32 {
 
 template <bool SPLIT>
 __device__ inline float speed32(const St32& s) {
-  return SPLIT ? s.vb + s.vi : s.vb;
+  return SPLIT ? s.vb + s.vi : s.vi;
 }
 
 template <int FORM, int K, bool SPLIT>
@@ -1555,10 +1568,7 @@ __device__ inline void block32(St32& s, const L32& c, float tk) {
       m = c.tdm;
     const float acc = fmaf(c.nkd, q, m);
     s.p = fmaf(c.dt, v, s.p);
-    if (SPLIT)
-      s.vi = fmaf(c.dt, acc, s.vi);
-    else
-      s.vb = fmaf(c.dt, acc, s.vb);
+    s.vi = fmaf(c.dt, acc, s.vi);
     if (FORM == FORM_G || FORM == FORM_F) s.e = fmaf(c.nkt, s.e, s.e);
   }
 }
@@ -1578,17 +1588,13 @@ __device__ inline void flush32(St32& s, bool split) {
   s.p = 0.0f;
 }
 
-template <bool SPLIT>
 __device__ inline void step32(St32& s, const L32& c, bool braking) {
-  const float v = speed32<SPLIT>(s);
+  const float v = speed32<true>(s);
   const float q = v * v;
   const float m = fmaxf(s.e + (braking ? c.tb : c.td), c.alc);
   const float acc = fmaf(c.nkd, q, m);
   s.p = fmaf(c.dt, v, s.p);
-  if (SPLIT)
-    s.vi = fmaf(c.dt, acc, s.vi);
-  else
-    s.vb = fmaf(c.dt, acc, s.vb);
+  s.vi = fmaf(c.dt, acc, s.vi);
   s.e = fmaf(c.nkt, s.e, s.e);
 }
 
@@ -1597,93 +1603,151 @@ __device__ inline void step32(St32& s, const L32& c, bool braking) {
 constexpr double SPLIT_STEPS = 6000.0;
 
 // Speed compensation is a per-lane property (its predicted length), so a
-// lane's arithmetic never depends on its wavefront; a wavefront holding both
-// kinds runs each form under its lane mask.
+// lane's arithmetic never depends on its wavefront.
 template <int FORM, int K>
-__device__ inline void block32_any(St32& s, const L32& c, float tk, bool split) {
-  if (__all(split)) {
-    block32<FORM, K, true>(s, c, tk);
-  } else if (__all(!split)) {
+HOT void block32_any(St32& s, const L32& c, float tk, lanes_t splits) {
+  if (splits == 0)
     block32<FORM, K, false>(s, c, tk);
-  } else {
-    if (split) block32<FORM, K, true>(s, c, tk);
-    if (!split) block32<FORM, K, false>(s, c, tk);
+  else
+    block32<FORM, K, true>(s, c, tk);
+}
+
+// Lane state and lane sets of the compensated FP32 integration (see Wave64).
+struct Wave32 {
+  St32 s;
+  lanes_t active, crossed, pend, stopped, clamped, free_lane;
+};
+
+// Block start states in LDS, as Saves64.
+template <int OBS>
+struct Saves32 {
+  static constexpr int SLOTS = OBS == AEB_OBS_STATIONARY ? 3 : 2;
+  float vb[SLOTS][ROLL_MAX], vi[SLOTS][ROLL_MAX], e[SLOTS][ROLL_MAX], p[SLOTS][ROLL_MAX];
+  float hi[SLOTS][ROLL_MAX], lo[SLOTS][ROLL_MAX];
+  int k[2][ROLL_MAX], end[2][ROLL_MAX];  // of slots SAV_END, SAV_PASS
+};
+
+template <int OBS>
+HOT void save_start32(const Wave32& L, Saves32<OBS>& S) {
+  const int t = threadIdx.x;
+  S.vb[SAV_CUR][t] = L.s.vb;
+  S.vi[SAV_CUR][t] = L.s.vi;
+  S.e[SAV_CUR][t] = L.s.e;
+  S.p[SAV_CUR][t] = L.s.p;
+  S.hi[SAV_CUR][t] = L.s.X.hi;
+  S.lo[SAV_CUR][t] = L.s.X.lo;
+}
+
+template <int OBS>
+HOT void keep_start32(Saves32<OBS>& S, int slot, int k, int B) {
+  const int t = threadIdx.x;
+  S.vb[slot][t] = S.vb[SAV_CUR][t];
+  S.vi[slot][t] = S.vi[SAV_CUR][t];
+  S.e[slot][t] = S.e[SAV_CUR][t];
+  S.p[slot][t] = S.p[SAV_CUR][t];
+  S.hi[slot][t] = S.hi[SAV_CUR][t];
+  S.lo[slot][t] = S.lo[SAV_CUR][t];
+  S.k[slot - 1][t] = k;
+  S.end[slot - 1][t] = k + B;
+}
+
+// What happened to the lanes in the block of B steps from step k (see
+// block_events of the FP64 kernel).
+template <int OBS>
+HOT void block_events32(Wave32& L, Saves32<OBS>& S, const L32& c, int k, int B,
+                        int impact_exit) {
+  const lanes_t stop = ballot(speed32<true>(L.s) <= 0.0f) & L.active;
+  lanes_t hit = 0;
+  if (OBS == AEB_OBS_STATIONARY)
+    hit = ballot((L.s.X.hi - L.s.X.lo) + L.s.p > c.gapf) & L.active & ~stop & ~L.crossed;
+  L.crossed |= hit;
+  L.pend |= hit;
+  L.stopped |= stop;
+  L.active &= ~(stop | (impact_exit ? hit : 0ull));
+  if (hit | stop) {
+    if (OBS == AEB_OBS_STATIONARY && in(hit))
+      keep_start32<OBS>(S, impact_exit ? SAV_END : SAV_PASS, k, B);
+    if (in(stop)) keep_start32<OBS>(S, SAV_END, k, B);
+    lanes_join();
   }
 }
 
-struct Lane32 {
-  St32 s, sv;  // state, and start state of the block where the obstacle was passed
-  int sk, sb;  // step index at that block start, and the block's length
-  bool active, crossed, pend, clamped, free_lane;
-};
+// The lanes whose speed cannot rise over the next block (see falling of the
+// FP64 kernel): the actuator's deviation from the command decays from above,
+// so the brake term m only falls, and m is below zero.  With the speed split
+// into base and increment the flush may move the read speed by the rounding of
+// the increment; the bound on m keeps each step's change well above that.
+HOT lanes_t falling32(const St32& s, const L32& c, float tk) {
+  return ballot(c.nkd <= 0.0f && c.nkt <= 0.0f && c.nkt >= -1.0f && s.e >= 0.0f &&
+                fmaxf(s.e + tk, c.alc) < -1e-2f);
+}
 
-template <int OBS, int B>
-__device__ inline void run_block32(Lane32& L, const L32& c, bool split, int nd, int k, int wnd,
-                                   int impact_exit) {
-  if (OBS == AEB_OBS_STATIONARY && !L.crossed) {
-    L.sv = L.s;
-    L.sk = k;
-    L.sb = B;
-  }
+template <int OBS, int B, bool TOP>
+HOT void run_block32(Wave32& L, Saves32<OBS>& S, const L32& c, bool split, lanes_t splits, int nd,
+                     int k, int wnd, int impact_exit) {
+  save_start32<OBS>(L, S);
   // blocks never straddle nd: the lane's target is fixed for the block
   const float tk = k >= nd ? c.tb : c.td;
   if (k + B <= wnd) {
-    block32_any<FORM_D, B>(L.s, c, tk, split);
-  } else if (__all(!L.active || L.clamped)) {
-    block32_any<FORM_C, B>(L.s, c, tk, split);
-  } else if (__all(!L.active || L.free_lane)) {
-    block32_any<FORM_F, B>(L.s, c, tk, split);
+    block32_any<FORM_D, B>(L.s, c, tk, splits);
+  } else if (!TOP && (L.active & ~L.clamped) == 0) {
+    block32_any<FORM_C, B>(L.s, c, tk, splits);
+  } else if (!TOP && (L.active & ~L.free_lane) == 0) {
+    block32_any<FORM_F, B>(L.s, c, tk, splits);
   } else {
-    block32_any<FORM_G, B>(L.s, c, tk, split);
-    L.clamped = L.clamped || (k + B > nd && L.s.e + c.tb <= c.alc);
+    block32_any<FORM_G, B>(L.s, c, tk, splits);
+    L.clamped |= ballot(k + B > nd && L.s.e + c.tb <= c.alc);
   }
   if ((k + B) % FLUSH == 0) flush32(L.s, split);
-  if (OBS == AEB_OBS_STATIONARY && L.active && !L.crossed &&
-      (L.s.X.hi - L.s.X.lo) + L.s.p > c.gapf) {
-    L.crossed = true;
-    L.pend = true;
-    if (impact_exit) L.active = false;
-  }
+  block_events32<OBS>(L, S, c, k, B, impact_exit);
 }
 
-// Consecutive K-step blocks in one steady form and one speed representation
-// (as run_steady of the FP64 kernel), with the flush at every flush point.
+// (see long_block of the FP64 kernel; thr: the speed above which no lane can
+// stop inside the block)
+HOT bool long_block32(const Wave32& L, float thr, lanes_t fall) {
+  const float v = speed32<true>(L.s);
+  const lanes_t low = ballot(v <= thr) & L.active;
+  if (low == 0) return true;
+  return (low & ~fall) == 0 && (ballot(v > 2.0f * thr) & L.active) != 0;
+}
+
+// Consecutive K-step blocks in one steady form, SPLIT if any lane's speed is
+// split (as run_steady of the FP64 kernel), with the flush at every flush
+// point.  (Two blocks per round of tests, the second in a rolled loop: no
+// faster for one wavefront on its SIMD, and 35 more VGPRs.)
 template <int OBS, int K, int FORM, bool SPLIT>
-__device__ inline int run_steady32(Lane32& L, const L32& c, float tk, int k, int wl,
-                                   int impact_exit) {
+HOT int run_steady32(Wave32& L, Saves32<OBS>& S, const L32& c, float tk, bool split, int k,
+                     int wl, lanes_t fall, int impact_exit) {
+  bool more;
   do {
-    const St32 b = L.s;
+    k = __builtin_amdgcn_readfirstlane(k);
+    save_start32<OBS>(L, S);
 #pragma unroll
     for (int q = 0; q < K / 16; ++q) {
       block32<FORM, 16, SPLIT>(L.s, c, tk);
       asm volatile("" : "+v"(L.s.p));  // no position update sunk to the end of the run
     }
-    if ((k + K) % FLUSH == 0) flush32(L.s, SPLIT);
-    if (OBS == AEB_OBS_STATIONARY && L.active && !L.crossed &&
-        (L.s.X.hi - L.s.X.lo) + L.s.p > c.gapf) {
-      L.sv = b;
-      L.sk = k;
-      L.sb = K;
-      L.crossed = true;
-      L.pend = true;
-      if (impact_exit) L.active = false;
-    }
+    if (K == FLUSH || (k + K) % FLUSH == 0) flush32(L.s, SPLIT && split);
+    block_events32<OBS>(L, S, c, k, K, impact_exit);
     k += K;
-  } while (k + K <= wl && __any(L.active) && !__any(L.active && speed32<SPLIT>(L.s) <= c.thr));
+    more = k + K <= wl && L.active != 0 && long_block32(L, c.thr, fall);
+  } while (more);
   return k;
 }
 
 template <int OBS, int K, bool BATCH>
-__global__ __launch_bounds__(256) void k_roll_fp32c(const Job* __restrict__ jobs,
+__global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__ jobs,
                                                     const uint32_t* __restrict__ perm, int64_t n,
                                                     Ctx ctx, double band_abs, double band_rel,
                                                     uint32_t* fix, unsigned long long* counter,
                                                     int persistent) {
   if (ctx.hdr) n = ctx.hdr->total;  // a recorded mix: its size from the device header
+  // the block ladder of the FP64 kernel, blocks starting on multiples of their length
   constexpr int KS = 4;
   constexpr int KM = K >= 64 ? 16 : KS;  // middle level of the block ladder
   static_assert(FLUSH % K == 0 && K % KM == 0 && KM % KS == 0,
                 "flush points must fall on block ends");
+  __shared__ Saves32<OBS> sav;
   for (int pass = 0;; ++pass) {
     const int64_t base = next_chunk(counter, persistent, pass, n);
     if (base >= n) break;
@@ -1701,8 +1765,7 @@ __global__ __launch_bounds__(256) void k_roll_fp32c(const Job* __restrict__ jobs
     const LaneScn sc = BATCH ? lane_scn<BATCH>(ctx, J, valid, g)
                              : lane_values(lane_scn<BATCH>(ctx, J, valid, g));
     const int nd = sc.nd, nmax = sc.nmax;
-    const bool varnd = true;
-    const int wnd = __builtin_amdgcn_readfirstlane(varnd ? wave_min(valid ? nd : INT_MAX) : nd);
+    const int wnd = __builtin_amdgcn_readfirstlane(wave_min(valid ? nd : INT_MAX));
     L32 c;  // (the speed read below is base + increment; the increment is 0 without compensation)
     c.dt = static_cast<float>(sc.dt);
     c.nkd = static_cast<float>(J.nkd);
@@ -1718,113 +1781,157 @@ __global__ __launch_bounds__(256) void k_roll_fp32c(const Job* __restrict__ jobs
     const float thr_s = static_cast<float>(static_cast<double>(KS) * sc.dt * J.dmax);
     const double band = band_abs + band_rel * fabs(J.gap);
     const bool split = J.pred > SPLIT_STEPS;  // per lane
-    Lane32 L;
-    L.s.vb = static_cast<float>(J.v0);
-    L.s.vi = split ? static_cast<float>(J.v0 - static_cast<double>(L.s.vb)) : 0.0f;
+    const lanes_t splits = ballot(split);
+    Wave32 L;
+    const float v0f = static_cast<float>(J.v0);
+    L.s.vb = split ? v0f : 0.0f;
+    L.s.vi = split ? static_cast<float>(J.v0 - static_cast<double>(v0f)) : v0f;
     L.s.e = 0.0f;
     L.s.p = 0.0f;
-    L.sv = L.s;
-    L.sk = 0;
-    L.sb = K;
-    L.active = valid;
-    L.crossed = L.pend = L.clamped = false;
-    L.free_lane = J.alim < sc.a_cmd - 1e-6;
+    L.active = ballot(valid);
+    L.crossed = L.pend = L.stopped = L.clamped = 0;
+    L.free_lane = ballot(J.alim < sc.a_cmd - 1e-6);
     const int impact_exit = ctx.impact_exit;
     bool boundary = false;
     int end = 0, steps = 0;
     double dist = 0.0;
     float vimp = 0.0f;
     int k = 0, wl = -1;
-    for (;;) {
+    while (L.active) {
       // the step index is the same in every lane: keep it (and the branches on it) scalar
       k = __builtin_amdgcn_readfirstlane(k);
-      if (!__any(L.active)) break;
-      if (!varnd || k >= wl) wl = wave_lim(varnd, L.active, k, nd, nmax);
+      if (k >= wl) wl = wave_lim(true, in(L.active), k, nd, nmax);
       // the command switches on at step nd: e = a - cmd jumps by -a_cmd.  Blocks
       // never straddle nd, so every lane passes through k == nd at a loop top.
-      if (k == nd) L.s.e += c.ejump;
+      L.s.e += k == nd ? c.ejump : 0.0f;
       const float v_now = speed32<true>(L.s);
+      const float tk = k >= nd ? c.tb : c.td;
+      lanes_t fall = ~0ull;
+      if (ballot(v_now <= c.thr) & L.active) fall = falling32(L.s, c, tk);
       // blocks start on multiples of their length, so flush points fall on block ends
-      if (k % K == 0 && k + K <= wl && !__any(L.active && v_now <= c.thr)) {
-        // past every lane's dead time, in a form no later block changes, no
-        // lane with the compensated speed: a run of blocks.  Without an
-        // obstacle only (measured: with one the run loses to single blocks,
-        // and runs for compensated-speed lanes cost more registers than they
-        // save)
-        const bool past = OBS == AEB_OBS_NONE && k + K > wnd;
-        const bool no_split = __all(!split);
-        const bool steady_c = past && __all(!L.active || L.clamped);
-        const bool steady_f = past && !steady_c && __all(!L.active || L.free_lane);
-        const float tk = k >= nd ? c.tb : c.td;
+      if (k % K == 0 && k + K <= wl && long_block32(L, c.thr, fall)) {
+        // past every lane's dead time, in a form no later block changes: a run
+        // of blocks
+        const lanes_t f = falling32(L.s, c, tk);
+        const bool past = k + K > wnd;
+        const bool no_split = (splits & L.active) == 0;
+        const bool steady_c = past && (L.active & ~L.clamped) == 0;
+        const bool steady_f = past && !steady_c && (L.active & ~L.free_lane) == 0;
+        const bool steady_g = past && (L.active & ~(L.clamped | L.free_lane)) == 0;
         if (steady_c && no_split) {
-          k = run_steady32<OBS, K, FORM_C, false>(L, c, tk, k, wl, impact_exit);
+          k = run_steady32<OBS, K, FORM_C, false>(L, sav, c, tk, split, k, wl, f, impact_exit);
         } else if (steady_f && no_split) {
-          k = run_steady32<OBS, K, FORM_F, false>(L, c, tk, k, wl, impact_exit);
+          k = run_steady32<OBS, K, FORM_F, false>(L, sav, c, tk, split, k, wl, f, impact_exit);
+        } else if (steady_c) {
+          k = run_steady32<OBS, K, FORM_C, true>(L, sav, c, tk, split, k, wl, f, impact_exit);
+        } else if (steady_f) {
+          k = run_steady32<OBS, K, FORM_F, true>(L, sav, c, tk, split, k, wl, f, impact_exit);
+        } else if (steady_g) {  // both kinds: the generic form, whose step serves either
+          k = run_steady32<OBS, K, FORM_G, true>(L, sav, c, tk, split, k, wl, f, impact_exit);
         } else {
-          run_block32<OBS, K>(L, c, split, nd, k, wnd, impact_exit);
+          run_block32<OBS, K, true>(L, sav, c, split, splits & L.active, nd, k, wnd, impact_exit);
           k += K;
         }
       } else if (KM > KS && k % KM == 0 && k + KM <= wl &&
-                 !__any(L.active && v_now <= thr_m)) {
-        run_block32<OBS, KM>(L, c, split, nd, k, wnd, impact_exit);
+                 (ballot(v_now <= thr_m) & L.active & ~fall) == 0) {
+        run_block32<OBS, KM, false>(L, sav, c, split, splits & L.active, nd, k, wnd, impact_exit);
         k += KM;
-      } else if (k % KS == 0 && k + KS <= wl && !__any(L.active && v_now <= thr_s)) {
-        run_block32<OBS, KS>(L, c, split, nd, k, wnd, impact_exit);
+      } else if (k % KS == 0 && k + KS <= wl &&
+                 (ballot(v_now <= thr_s) & L.active & ~fall) == 0) {
+        run_block32<OBS, KS, false>(L, sav, c, split, splits & L.active, nd, k, wnd, impact_exit);
         k += KS;
       } else {
-        if (L.active) {
+        bool clamp = false, cross = false, done = false;
+        if (in(L.active)) {
           const float vb = v_now;
-          if (split) step32<true>(L.s, c, k >= nd);
-          if (!split) step32<false>(L.s, c, k >= nd);
+          step32(L.s, c, k >= nd);
           if ((k + 1) % FLUSH == 0) flush32(L.s, split);
-          if (k >= nd) L.clamped = L.clamped || (L.s.e + c.tb <= c.alc);
+          clamp = k >= nd && L.s.e + c.tb <= c.alc;
           const float v = speed32<true>(L.s);
-          if (OBS == AEB_OBS_STATIONARY && !L.crossed && (L.s.X.hi - L.s.X.lo) + L.s.p > c.gapf) {
-            L.crossed = true;
+          if (OBS == AEB_OBS_STATIONARY && !in(L.crossed) &&
+              (L.s.X.hi - L.s.X.lo) + L.s.p > c.gapf) {
+            cross = true;
             vimp = v;
             if (impact_exit) {
-              L.active = false;
               end = AEB_END_IMPACT;
-              steps = k + 1;
-              dist = L.s.X.value(L.s.p);
+              const double x = L.s.X.value(L.s.p);
               const double step_len = static_cast<double>(c.dt) * static_cast<double>(vb);
-              boundary = fabs(dist - J.gap) < band || fabs(J.gap - (dist - step_len)) < band;
+              boundary = fabs(x - J.gap) < band || fabs(J.gap - (x - step_len)) < band;
             }
           }
-          if (L.active) {
-            if (v <= 0.0f) {
-              L.active = false;
+          if (end == 0) {
+            if (v <= 0.0f)
               end = AEB_END_STOP;
-              steps = k + 1;
-              dist = L.s.X.value(L.s.p);
-            } else if (k + 1 == nmax) {
-              L.active = false;
+            else if (k + 1 == nmax)
               end = AEB_END_HORIZON;
-              steps = k + 1;
-              dist = L.s.X.value(L.s.p);
-            }
+          }
+          done = end != 0;
+          if (done) {
+            steps = k + 1;
+            dist = L.s.X.value(L.s.p);
           }
         }
+        lanes_join();
+        L.clamped |= ballot(clamp);
+        if (OBS == AEB_OBS_STATIONARY) L.crossed |= ballot(cross);
+        L.active &= ~ballot(done);
         k += 1;
       }
     }
-    // replay the block in which each pending lane passed the obstacle, single
-    // steps with the per-step test; the crossing recurs within the block (at its
-    // last step at the latest, where the block-end test fired)
-    if (OBS == AEB_OBS_STATIONARY && __any(L.pend)) {
-      St32 r = L.sv;
-      int kr = L.sk;
+    // replay the blocks in which lanes passed the obstacle, and those in which
+    // they stopped (see the FP64 kernel): chunks of RB steps that hold no event
+    // whole, then single steps with every test.  The crossing recurs within the
+    // block (at its last step at the latest, where the block-end test fired).
+    auto replay = [&](lanes_t who, int slot, bool to_stop) {
+      const int t = threadIdx.x;
+      bool go = in(who);
+      St32 r = L.s;
+      int kr = 0, se = 0;
+      if (go) {
+        r.vb = sav.vb[slot][t];
+        r.vi = sav.vi[slot][t];
+        r.e = sav.e[slot][t];
+        r.p = sav.p[slot][t];
+        r.X.hi = sav.hi[slot][t];
+        r.X.lo = sav.lo[slot][t];
+        kr = sav.k[slot - 1][t];
+        se = sav.end[slot - 1][t];
+      }
+      // a stopped lane may also have passed the obstacle in the same block
+      bool seek = OBS == AEB_OBS_STATIONARY && (!to_stop || !in(L.crossed));
+      bool passed = false;
+      constexpr int RB = 8;
+      if (K > RB) {
+        const float tk = kr >= nd ? c.tb : c.td;  // one target over a block
+        bool skip = go;
+        for (int it = 0; it < K / RB; ++it) {
+          skip = skip && kr % RB == 0 && kr + RB <= se;
+          if (ballot(skip) == 0) break;
+          if (skip) {
+            St32 q = r;
+            block32<FORM_G, RB, true>(q, c, tk);
+            if ((kr + RB) % FLUSH == 0) flush32(q, split);
+            if ((seek && (q.X.hi - q.X.lo) + q.p > c.gapf) ||
+                (to_stop && speed32<true>(q) <= 0.0f)) {
+              skip = false;
+            } else {
+              r = q;
+              kr += RB;
+            }
+          }
+        }
+      }
       for (int it = 0; it < K; ++it) {
-        if (!__any(L.pend)) break;
-        if (L.pend) {
+        if (ballot(go) == 0) break;
+        if (go) {
           const float vb = speed32<true>(r);
-          if (split) step32<true>(r, c, kr >= nd);
-          if (!split) step32<false>(r, c, kr >= nd);
+          step32(r, c, kr >= nd);
           ++kr;
           if (kr % FLUSH == 0) flush32(r, split);
           const float v = speed32<true>(r);
-          if ((r.X.hi - r.X.lo) + r.p > c.gapf || it == L.sb - 1) {
-            L.pend = false;
+          if (seek && ((r.X.hi - r.X.lo) + r.p > c.gapf || (!to_stop && kr == se))) {
+            passed = true;
+            seek = false;
             vimp = v;
             if (impact_exit) {
               end = AEB_END_IMPACT;
@@ -1832,18 +1939,31 @@ __global__ __launch_bounds__(256) void k_roll_fp32c(const Job* __restrict__ jobs
               dist = r.X.value(r.p);
               const double step_len = static_cast<double>(c.dt) * static_cast<double>(vb);
               boundary = fabs(dist - J.gap) < band || fabs(J.gap - (dist - step_len)) < band;
+              go = false;
             }
+            if (!to_stop) go = false;
+          }
+          if (to_stop && go && (v <= 0.0f || kr == se)) {
+            end = AEB_END_STOP;
+            steps = kr;
+            dist = r.X.value(r.p);
+            go = false;
           }
         }
       }
-    }
-    bool collided = L.crossed;
+      lanes_join();
+      if (OBS == AEB_OBS_STATIONARY) L.crossed |= ballot(passed);
+    };
+    if (OBS == AEB_OBS_STATIONARY && L.pend)
+      replay(L.pend, impact_exit ? SAV_END : SAV_PASS, false);
+    if (L.stopped) replay(L.stopped, SAV_END, true);
+    bool collided = in(L.crossed);
     if (OBS == AEB_OBS_STATIONARY && !impact_exit) {
       // the flag is decided in FP64 on the compensated distance
       collided = dist > J.gap;
       boundary = fabs(J.gap - dist) < band;
-      if (collided != L.crossed) vimp = 0.0f;
-    } else if (OBS == AEB_OBS_STATIONARY && !L.crossed) {
+      if (collided != in(L.crossed)) vimp = 0.0f;
+    } else if (OBS == AEB_OBS_STATIONARY && !in(L.crossed)) {
       boundary = J.gap - dist < band;
     }
     if (ctx.lanes) count_lanes(ctx.lanes, k, 64);

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2604_27193_amd import workloads as W
-from test_gpu_parity import check_fp64, plain, to_np, upload
+from test_gpu_parity import check_fp32c, check_fp64, plain, to_np, upload
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +78,28 @@ def test_stop_and_crossing_in_one_block(B, orc):
         d2 = dict(d, **over)
         check_fp64(to_np(B.rollout(d2, params=upload(cols))), orc.rollout_given(d2, cols),
                    exact=True)
+
+
+@pytest.mark.parametrize("n", [65, 1031])
+@pytest.mark.parametrize("name", ["wide", "wide_exit", "wide_none"])
+def test_scattered_stops_fp32c(B, orc, name, n):
+    """The compensated form on the same scattered stops, speeds split into base
+    and increment (long rollouts) and whole in one wavefront."""
+    d = W.single(n, seed=11, scenario_id=n, **VARIANTS[name])
+    check_fp32c(to_np(B.rollout(d, precision="fp32c")), orc.run(d))
+
+
+@pytest.mark.parametrize("name", ["wide", "wide_exit", "wide_none", "downhill", "late_command",
+                                  "short_horizon", "perception"])
+def test_grouping_does_not_change_bits_fp32c(B, name):
+    """A sample's result does not depend on its wavefront: every sample of a
+    launch equals the same sample in a launch of its own 64."""
+    d = W.single(1031, seed=12, **VARIANTS[name])
+    cols = B.sample_params(d, device=False)
+    whole = to_np(B.rollout(d, params=upload(cols), precision="fp32c"))
+    for a in range(0, 1031, 64):
+        part = {k: v[a:a + 64] for k, v in cols.items()}
+        got = to_np(B.rollout(dict(d, n_samples=len(part["v0"])), params=upload(part),
+                              precision="fp32c"))
+        for k in got:
+            assert np.array_equal(got[k], whole[k][a:a + 64]), (k, a)
