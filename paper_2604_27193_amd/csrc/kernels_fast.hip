@@ -144,6 +144,14 @@ __device__ inline float predict_ctl_stop_time(float v0, float gap, float tw, flo
   return t_b + predict_stop_time(v_b, kd, c, alim, tau, acmd, dead);
 }
 
+// The actuator's stage values of one RK4 step from a1, and its end value.
+struct RkAct {
+  double a2, a3, a4, end;
+};
+__device__ inline RkAct rk4_act(double a1, double kt, double dt, double h2, double h6, double cmd);
+constexpr int ACT_HDR = 8;    // doubles in front of the actuator table's entries: `fix`
+constexpr int ACT_PAD = 64;   // entries written past the last step or `fix`
+
 // Inputs of the prep stage: one scenario (uniform) or a batch table.
 struct PrepArgs {
   aeb_scenario s;          // single scenario
@@ -158,6 +166,7 @@ struct PrepArgs {
   int ctl;                   // closed-loop controller (single scenario)
   double* weight;            // single scenario: importance-sampling weights out (or null)
   const BatchHdr* hdr;       // batch on device tables: n, cap and n_scn from here (else null)
+  double* act;               // single scenario: the actuator table to fill (or null)
 };
 
 // One sample: its parameters (drawn, or loaded from the plain method's
@@ -260,6 +269,45 @@ HOT uint32_t prep_sample(const PrepArgs& a, int64_t i, uint32_t j, int64_t local
   return key;
 }
 
+// The actuator table (ActTab) of a scenario with a CONST time constant, by one
+// lane: a serial chain of about twenty operations per step (50 ns) over the
+// steps of the horizon or until the actuator stands still (32 time constants
+// or so), beside the prep of the samples.  In groups of FG steps, tested once
+// each: entries past the last step are never read, and entries past `fix` all
+// equal it.
+__device__ inline void fill_act(const aeb_scenario& s, int nd, int nmax, double* act) {
+  constexpr int FG = 16;
+  static_assert(ACT_PAD >= 3 * FG, "a group past the last step, and two past `fix`");
+  const double dt = s.dt, cmd = s.a_cmd, kt = 1.0 / s.tau.p0;  // as in the job records
+  const double h2 = 0.5 * dt, h6 = dt / 6.0;
+  const int n = nd < nmax ? nmax - nd : 0;  // braking steps
+  double* tb = act + ACT_HDR;
+  double a = 0.0;
+  auto entry = [&](int i) {
+    const RkAct r = rk4_act(a, kt, dt, h2, h6, cmd);
+    tb[4 * i] = a;
+    tb[4 * i + 1] = r.a2;
+    tb[4 * i + 2] = r.a3;
+    tb[4 * i + 3] = r.a4;
+    return r.end;
+  };
+  int i = 0;
+  bool still = false;
+  while (i < n && !still) {
+    double before = a;
+#pragma unroll
+    for (int j = 0; j < FG; ++j) {
+      before = a;
+      a = entry(i + j);
+    }
+    i += FG;
+    still = a == before;  // a step that changes nothing: none later does
+  }
+  // the reads that start at `fix`: a block and the entries loaded ahead of it
+  for (int j = 0; j < 2 * FG; ++j) entry(i + j);
+  *reinterpret_cast<int*>(act) = i;
+}
+
 template <bool DEVRNG, bool BATCH>
 __global__ __launch_bounds__(prep_threads<DEVRNG>()) void k_prep(PrepArgs a, Job* jobs,
                                                                  LeadJob* leads, uint32_t* keys) {
@@ -269,7 +317,15 @@ __global__ __launch_bounds__(prep_threads<DEVRNG>()) void k_prep(PrepArgs a, Job
   const float capf = a.hdr ? a.hdr->cap : a.cap;
   const int n_scn = a.hdr ? a.hdr->n_scn : a.n_scn;
   if (!BATCH) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * NT + threadIdx.x;
+    int64_t blk = blockIdx.x;
+    if (a.act) {  // the first block fills the actuator table
+      if (blk == 0) {
+        if (threadIdx.x == 0) fill_act(a.s, a.nd, a.nmax, a.act);
+        return;
+      }
+      --blk;
+    }
+    const int64_t i = blk * NT + threadIdx.x;
     if (i < n_all) keys[i] = prep_sample<DEVRNG, false>(a, i, 0u, i, capf, jobs, leads);
     return;
   }
@@ -459,27 +515,52 @@ __device__ inline double rk_dv(const Job& J, double v, double a) {
   return (m + J.nkd * (v * v)) - J.c;
 }
 
-template <int FORM>
-__device__ inline void rk4_step(St64& s, const Job& J, double dt, double h2, double h6,
+// (k1 + 2 k2 + 2 k3 + k4): the doubled stages come in by fused multiply-adds,
+// the same bits as a product and a sum, since doubling is exact; two operations
+// less in each of the three sums.
+__device__ inline double rk_sum(double k1, double k2, double k3, double k4) {
+  return fma(2.0, k3, fma(2.0, k2, k1)) + k4;
+}
+
+__device__ inline RkAct rk4_act(double a1, double kt, double dt, double h2, double h6,
                                 double cmd) {
+  RkAct r;
+  const double k1 = (cmd - a1) * kt;
+  r.a2 = a1 + h2 * k1;
+  const double k2 = (cmd - r.a2) * kt;
+  r.a3 = a1 + h2 * k2;
+  const double k3 = (cmd - r.a3) * kt;
+  r.a4 = a1 + dt * k3;
+  const double k4 = (cmd - r.a4) * kt;
+  r.end = a1 + h6 * rk_sum(k1, k2, k3, k4);
+  return r;
+}
+
+// TAB: the actuator's stage values come from tb (see ActTab) and the lane's own
+// actuator is left alone.
+template <int FORM, bool TAB = false>
+__device__ inline void rk4_step(St64& s, const Job& J, double dt, double h2, double h6,
+                                double cmd, const double* tb = nullptr) {
   constexpr bool ACT = FORM == FORM_G || FORM == FORM_F;  // the actuator is read
-  const double v1 = s.v, a1 = s.a;
-  const double k1v = rk_dv<FORM>(J, v1, a1);
-  const double k1a = ACT ? (cmd - a1) * J.kt : 0.0;
-  const double v2 = v1 + h2 * k1v, a2 = ACT ? a1 + h2 * k1a : a1;
-  const double k2v = rk_dv<FORM>(J, v2, a2);
-  const double k2a = ACT ? (cmd - a2) * J.kt : 0.0;
-  const double v3 = v1 + h2 * k2v, a3 = ACT ? a1 + h2 * k2a : a1;
-  const double k3v = rk_dv<FORM>(J, v3, a3);
-  const double k3a = ACT ? (cmd - a3) * J.kt : 0.0;
-  const double v4 = v1 + dt * k3v, a4 = ACT ? a1 + dt * k3a : a1;
-  const double k4v = rk_dv<FORM>(J, v4, a4);
-  s.x = s.x + h6 * (((v1 + 2.0 * v2) + 2.0 * v3) + v4);
-  s.v = v1 + h6 * (((k1v + 2.0 * k2v) + 2.0 * k3v) + k4v);
-  if (ACT) {
-    const double k4a = (cmd - a4) * J.kt;
-    s.a = a1 + h6 * (((k1a + 2.0 * k2a) + 2.0 * k3a) + k4a);
+  const double v1 = s.v;
+  double a1 = s.a;
+  RkAct act{a1, a1, a1, a1};
+  if (ACT && TAB) {
+    a1 = tb[0];
+    act = RkAct{tb[1], tb[2], tb[3], s.a};
+  } else if (ACT) {
+    act = rk4_act(a1, J.kt, dt, h2, h6, cmd);
   }
+  const double k1v = rk_dv<FORM>(J, v1, a1);
+  const double v2 = v1 + h2 * k1v;
+  const double k2v = rk_dv<FORM>(J, v2, act.a2);
+  const double v3 = v1 + h2 * k2v;
+  const double k3v = rk_dv<FORM>(J, v3, act.a3);
+  const double v4 = v1 + dt * k3v;
+  const double k4v = rk_dv<FORM>(J, v4, act.a4);
+  s.x = s.x + h6 * rk_sum(v1, v2, v3, v4);
+  s.v = v1 + h6 * rk_sum(k1v, k2v, k3v, k4v);
+  if (ACT) s.a = act.end;
 }
 
 // Kernel tag of explicit Euler in the unfused form (the paper's rule of no
@@ -495,11 +576,51 @@ __device__ inline double mad(double a, double b, double c) {
   return NF ? a * b + c : fma(a, b, c);
 }
 
-template <int FORM, int K, bool LEAD, int INTEG = AEB_EULER>
-HOT void block64(St64& s, Ld64& l, const Job& J, double al, double dt, double cmd) {
+// The actuator's trajectory when every sample of the launch has the same
+// actuator time constant and command step (a CONST tau, no perception, no
+// controller): it is then the same for all of them, so the prep launch's first
+// block runs it once and the integration reads the values (scalar loads)
+// instead of updating every lane's actuator: 19 of 51 operations of an RK4 step.
+// Entry i holds step nd + i: the actuator at the step's start and its three
+// later stage values.  Entries repeat from `fix` on, where a step leaves the
+// actuator's bits as they are.  RK4 only: of an Euler step it would save 2 of 7
+// operations and add a load that comes too late (350,000 samples 0.46 against
+// 0.42 ms, 12,000 0.26 against 0.13).
+struct ActTab {
+  const double* __restrict__ tb;  // null: no table
+  int fix, nd;
+  HOT const double* at(int k) const { return tb + int64_t(4) * min(k - nd, fix); }
+};
+
+// TAB: the actuator from tb (K steps of entries), J's own left alone
+template <int FORM, int K, bool LEAD, int INTEG = AEB_EULER, bool TAB = false>
+HOT void block64(St64& s, Ld64& l, const Job& J, double al, double dt, double cmd,
+                 const double* tb = nullptr) {
   constexpr bool NF = INTEG == EULER_NOFMA;
   if (INTEG == AEB_RK4) {
     const double h2 = 0.5 * dt, h6 = dt / 6.0;
+    if (TAB) {
+      // entries two steps at a time, loaded two steps ahead: a scalar load
+      // takes longer than one step of a wavefront alone on its SIMD
+      double e[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) e[q] = tb[q];
+#pragma unroll
+      for (int j = 0; j < K; j += 2) {
+        double f[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) f[q] = tb[4 * (j + 2) + q];
+        __builtin_amdgcn_sched_barrier(0);
+        rk4_step<FORM, true>(s, J, dt, h2, h6, cmd, e);
+        asm volatile("" : "+v"(s.x));
+        rk4_step<FORM, true>(s, J, dt, h2, h6, cmd, e + 4);
+        asm volatile("" : "+v"(s.x));
+#pragma unroll
+        for (int q = 0; q < 8; ++q) e[q] = f[q];
+      }
+      static_assert(!TAB || K % 2 == 0, "step pairs");
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < K; ++j) {
       rk4_step<FORM>(s, J, dt, h2, h6, cmd);
@@ -837,24 +958,42 @@ HOT lanes_t falling(const Wave64& L, const Job& J, double cmd, double ktdt) {
                 fmax(L.s.a, J.alim) - J.c < -1e-3);
 }
 
+// B steps of one form from step k, in pieces of at most 16 (entries of the
+// actuator table are contiguous over a piece), the actuator taken over from the
+// table at the end so that tests, saves and checked steps find it in the lane.
+template <int FORM, int B, bool LEAD, int INTEG, bool TAB>
+HOT void steps64(Wave64& L, const Job& J, double al, double dt, double cmd, int k,
+                 const ActTab& at) {
+  if (!TAB || (FORM != FORM_F && FORM != FORM_G)) {
+    block64<FORM, B, LEAD, INTEG>(L.s, L.l, J, al, dt, cmd);
+    return;
+  }
+  constexpr int P = B < 16 ? B : 16;
+#pragma unroll
+  for (int q = 0; q < B / P; ++q)
+    block64<FORM, P, LEAD, INTEG, true>(L.s, L.l, J, al, dt, cmd, at.at(k + q * P));
+  static_assert(!TAB || B % P == 0, "whole pieces");
+  L.s.a = *at.at(k + B);
+}
+
 // wnd: the smallest nd of the wavefront's lanes (the whole block is dead time
 // for every lane when k + B <= wnd).  TOP: a block of the top level, where the
 // steady forms are the runs' business and only the dead time and the generic
 // form are left.
-template <int OBS, int B, int INTEG, bool CTL, bool TOP>
+template <int OBS, int B, int INTEG, bool CTL, bool TOP, bool TAB>
 HOT void run_block64(Wave64& L, Saves64<OBS>& S, const Job& J, double al, const LaneScn& c, int k,
-                     int wnd, int impact_exit, double a_warn, double& xmax) {
+                     int wnd, int impact_exit, double a_warn, double& xmax, const ActTab& at) {
   constexpr bool LEAD = OBS == AEB_OBS_LEAD;
   const double cmd = lane_cmd<CTL>(L, c, a_warn, k);
   save_start<OBS>(L, S);
   if (k + B <= wnd) {
-    block64<FORM_D, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
+    steps64<FORM_D, B, LEAD, INTEG, TAB>(L, J, al, c.dt, cmd, k, at);
   } else if (!TOP && (L.active & ~L.clamped) == 0) {
-    block64<FORM_C, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
+    steps64<FORM_C, B, LEAD, INTEG, TAB>(L, J, al, c.dt, cmd, k, at);
   } else if (!TOP && (L.active & ~L.free_lane) == 0) {
-    block64<FORM_F, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
+    steps64<FORM_F, B, LEAD, INTEG, TAB>(L, J, al, c.dt, cmd, k, at);
   } else {
-    block64<FORM_G, B, LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
+    steps64<FORM_G, B, LEAD, INTEG, TAB>(L, J, al, c.dt, cmd, k, at);
     L.clamped |= L.limited & ballot(k + B > first_cmd<CTL>(L, c) && L.s.a <= J.alim);
   }
   block_events<OBS>(L, S, J, k, B, impact_exit);
@@ -875,9 +1014,10 @@ HOT bool long_block(const Wave64& L, double thr, lanes_t fall) {
 // limited for good, or every one never limited), until the block limit wl or
 // until shorter blocks are the better choice.  Returns the step index after
 // the last block.
-template <int OBS, int K, int FORM, int INTEG>
+template <int OBS, int K, int FORM, int INTEG, bool TAB>
 HOT int run_steady(Wave64& L, Saves64<OBS>& S, const Job& J, double al, double dt, double cmd,
-                   int k, int wl, double thr, lanes_t fall, int impact_exit, double& xmax) {
+                   int k, int wl, double thr, lanes_t fall, int impact_exit, double& xmax,
+                   const ActTab& at) {
   constexpr bool LEAD = OBS == AEB_OBS_LEAD;
   bool more;
   do {
@@ -889,10 +1029,11 @@ HOT int run_steady(Wave64& L, Saves64<OBS>& S, const Job& J, double al, double d
     // update sunk to the end of the run (hundreds of registers)
 #pragma unroll
     for (int q = 0; q < K / 16; ++q) {
-      block64<FORM, 16, LEAD, INTEG>(L.s, L.l, J, al, dt, cmd);
+      steps64<FORM, 16, LEAD, INTEG, TAB>(L, J, al, dt, cmd, k + 16 * q, at);
       asm volatile("" : "+v"(L.s.x));
     }
     if (K % 16 != 0) block64<FORM, K % 16, LEAD, INTEG>(L.s, L.l, J, al, dt, cmd);
+    static_assert(!TAB || K % 16 == 0, "whole pieces");
     block_events<OBS>(L, S, J, k, K, impact_exit);
     if (INTEG == AEB_RK4) xmax = fmax(xmax, in(L.active) ? L.s.x : xmax);
     k += K;
@@ -901,12 +1042,15 @@ HOT int run_steady(Wave64& L, Saves64<OBS>& S, const Job& J, double al, double d
   return k;
 }
 
-template <int OBS, int K, bool BATCH, int INTEG = AEB_EULER, bool CTL = false>
+template <int OBS, int K, bool BATCH, int INTEG = AEB_EULER, bool CTL = false, bool TAB = false>
 __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ jobs,
                                                    const LeadJob* __restrict__ leads,
                                                    const uint32_t* __restrict__ perm, int64_t n,
                                                    Ctx ctx, unsigned long long* counter,
-                                                   int persistent) {
+                                                   int persistent,
+                                                   const double* __restrict__ act) {
+  ActTab at{nullptr, 0, 0};
+  if (TAB) at = ActTab{act + ACT_HDR, *reinterpret_cast<const int*>(act), ctx.nd};
   if (ctx.hdr) n = ctx.hdr->total;  // a recorded mix: its size from the device header
   // block ladder: K steps, then KM, then KS, then single checked steps.  A
   // level runs while every lane that could stop inside the block (speed below
@@ -1041,35 +1185,35 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
           // (a clamped lane's speed falls whenever its acceleration without
           // drag is below zero)
           const lanes_t f = ballot(J.nkd <= 0.0 && J.alim - J.c < -1e-3);
-          k = run_steady<OBS, K, FORM_C, INTEG>(L, sav, J, al, c.dt, 0.0, k, wl, thr_k, f,
-                                                ctx.impact_exit, xmax);
+          k = run_steady<OBS, K, FORM_C, INTEG, TAB>(L, sav, J, al, c.dt, 0.0, k, wl, thr_k, f,
+                                                ctx.impact_exit, xmax, at);
         } else if (past && (L.active & ~L.free_lane) == 0) {
           const double cmd = lane_cmd<CTL>(L, c, ctx.ca.a_warn, k);
           const lanes_t f = falling(L, J, cmd, ktdt);
-          k = run_steady<OBS, K, FORM_F, INTEG>(L, sav, J, al, c.dt, cmd, k, wl, thr_k, f,
-                                                ctx.impact_exit, xmax);
+          k = run_steady<OBS, K, FORM_F, INTEG, TAB>(L, sav, J, al, c.dt, cmd, k, wl, thr_k, f,
+                                                ctx.impact_exit, xmax, at);
         } else if (past && (L.active & ~(L.clamped | L.free_lane)) == 0) {
           // both kinds: the generic form, whose step serves either
           const double cmd = lane_cmd<CTL>(L, c, ctx.ca.a_warn, k);
           const lanes_t f = falling(L, J, cmd, ktdt);
-          k = run_steady<OBS, K, FORM_G, INTEG>(L, sav, J, al, c.dt, cmd, k, wl, thr_k, f,
-                                                ctx.impact_exit, xmax);
+          k = run_steady<OBS, K, FORM_G, INTEG, TAB>(L, sav, J, al, c.dt, cmd, k, wl, thr_k, f,
+                                                ctx.impact_exit, xmax, at);
         } else {
-          run_block64<OBS, K, INTEG, CTL, true>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
-                                          ctx.ca.a_warn, xmax);
+          run_block64<OBS, K, INTEG, CTL, true, TAB>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+                                          ctx.ca.a_warn, xmax, at);
           k += K;
         }
       } else if (KM > KS && k + KM <= wl && (ballot(L.s.v <= thr_m) & L.active & ~fall) == 0) {
-        run_block64<OBS, KM, INTEG, CTL, false>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
-                                         ctx.ca.a_warn, xmax);
+        run_block64<OBS, KM, INTEG, CTL, false, TAB>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+                                         ctx.ca.a_warn, xmax, at);
         k += KM;
       } else if (k + KS <= wl && (ballot(L.s.v <= thr_s) & L.active & ~fall) == 0) {
-        run_block64<OBS, KS, INTEG, CTL, false>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
-                                         ctx.ca.a_warn, xmax);
+        run_block64<OBS, KS, INTEG, CTL, false, TAB>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+                                         ctx.ca.a_warn, xmax, at);
         k += KS;
       } else if (K2 < KS && k + K2 <= wl && (ballot(L.s.v <= thr_2) & L.active & ~fall) == 0) {
-        run_block64<OBS, K2, INTEG, CTL, false>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
-                                         ctx.ca.a_warn, xmax);
+        run_block64<OBS, K2, INTEG, CTL, false, TAB>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
+                                         ctx.ca.a_warn, xmax, at);
         k += K2;
       } else {
         // checked single steps, in a loop of their own for as long as no
@@ -2363,7 +2507,38 @@ void sort_keys(const Bufs& b, int64_t n, hipStream_t st, const BatchHdr* hdr = n
 template <int OBS, int K, bool BATCH, int INTEG = AEB_EULER, bool CTL = false>
 void go64(const Shape& sh, const Bufs& b, int64_t n, const Ctx& ctx, hipStream_t st) {
   hipLaunchKernelGGL((k_roll_fp64<OBS, K, BATCH, INTEG, CTL>), dim3(sh.grid), dim3(sh.block), 0,
-                     st, b.jobs, b.leads, b.perm, n, ctx, b.counter, sh.persistent);
+                     st, b.jobs, b.leads, b.perm, n, ctx, b.counter, sh.persistent, nullptr);
+}
+
+// the RK4 integration on the launch's actuator table
+template <int OBS>
+void go64_act(const Shape& sh, const Bufs& b, int64_t n, const Ctx& ctx, const double* act,
+              hipStream_t st) {
+  hipLaunchKernelGGL((k_roll_fp64<OBS, 16, false, AEB_RK4, false, true>), dim3(sh.grid),
+                     dim3(sh.block), 0, st, b.jobs, b.leads, b.perm, n, ctx, b.counter,
+                     sh.persistent, act);
+}
+
+// Bytes of the actuator table (ActTab) of a launch of n samples, 0 where it is
+// not used.  One actuator for all samples: RK4 with a CONST time constant (host
+// columns may hold any), no perception, no controller.  From ACT_MIN samples:
+// below, a SIMD has a wavefront or two, whose speed is a serial chain that the
+// actuator's operations only accompany, and the table takes 0.25 ms to fill
+// (preset of the paper, rollout with and without it: 65,536 samples 1.25 and
+// 1.02 ms, 100,000 1.29 and 1.36, 350,000 2.30 and 2.78, 1,048,576 5.8 and
+// 7.7).  The table takes the space
+// of the command steps and the fix-up list, which such a launch leaves unused
+// (8 bytes a sample); a horizon that needs more keeps the plain form.
+constexpr int64_t ACT_MIN = 98304;
+size_t act_bytes(const aeb_scenario& s, int64_t n) {
+  if (s.integrator != AEB_RK4 || s.tau.kind != AEB_DIST_CONST || perception_on(s) ||
+      control_on(s) || n < ACT_MIN)
+    return 0;
+  const size_t steps = static_cast<size_t>(horizon_steps(s));
+  const size_t room = 8 * static_cast<size_t>(n);
+  if (steps >= room) return 0;
+  const size_t b = sizeof(double) * (ACT_HDR + 4 * (steps + ACT_PAD));
+  return b <= room ? b : 0;
 }
 
 template <int OBS, int K, bool BATCH>
@@ -2421,7 +2596,7 @@ inline void arm_lanes(Ctx& ctx, hipStream_t st) {
 
 template <bool BATCH>
 int integrate(const aeb_scenario& s0, int precision, const Bufs& b, int64_t n, const Ctx& ctx_in,
-              const ParamSrc* src, hipStream_t st) {
+              const ParamSrc* src, hipStream_t st, const double* act = nullptr) {
   const int obs = s0.obstacle;
   Ctx ctx = ctx_in;
   const TuneCfg t = tune_get(precision == AEB_FP64 ? AEB_FP64 : AEB_FP32C, obs);
@@ -2460,7 +2635,10 @@ int integrate(const aeb_scenario& s0, int precision, const Bufs& b, int64_t n, c
     // an RK4 step costs about eight Euler steps: short blocks keep the tail small
     arm_lanes(ctx, st);
     timing_begin(st);
-    if (obs == AEB_OBS_STATIONARY)
+    if (!BATCH && act)
+      obs == AEB_OBS_STATIONARY ? go64_act<AEB_OBS_STATIONARY>(sh, b, n, ctx, act, st)
+                                : go64_act<AEB_OBS_NONE>(sh, b, n, ctx, act, st);
+    else if (obs == AEB_OBS_STATIONARY)
       go64<AEB_OBS_STATIONARY, 16, BATCH, AEB_RK4>(sh, b, n, ctx, st);
     else
       go64<AEB_OBS_NONE, 16, BATCH, AEB_RK4>(sh, b, n, ctx, st);
@@ -2559,7 +2737,8 @@ int launch_rollout_fast_into(const aeb_scenario& s, const ParamSrc* src, int pre
   const bool lead = s.obstacle == AEB_OBS_LEAD;
   Bufs b;
   bufs_layout(n, 0, lead, static_cast<char*>(scratch_base), &b);
-  const unsigned pblk = prep_grid(n);
+  double* act = !src && act_bytes(s, n) > 0 ? reinterpret_cast<double*>(b.nds) : nullptr;
+  const unsigned pblk = prep_grid(n) + (act ? 1 : 0);
   const bool ctl = control_on(s);
   const int nb = ctl ? NBINS_CTL : NBINS;
   hipLaunchKernelGGL(k_zero, dim3(nb / 256), dim3(256), 0, st, b.hist, int64_t(nb));
@@ -2573,6 +2752,7 @@ int launch_rollout_fast_into(const aeb_scenario& s, const ParamSrc* src, int pre
   pa.nds = perception_on(s) ? b.nds : nullptr;
   pa.ctl = ctl ? 1 : 0;
   pa.weight = out.weight;
+  pa.act = act;
   const unsigned cblk = static_cast<unsigned>((n + PREP_SAMPLES - 1) / PREP_SAMPLES);
   if (src && ctl)
     hipLaunchKernelGGL(k_prep_cols<NBINS_CTL>, dim3(cblk), dim3(PREP_BLOCK), 0, st, pa, b.jobs,
@@ -2597,7 +2777,7 @@ int launch_rollout_fast_into(const aeb_scenario& s, const ParamSrc* src, int pre
   ctx.tab = nullptr;
   ctx.nds = pa.nds;
   ctx.ca = ctl_args(s);
-  return integrate<false>(s, precision, b, n, ctx, src, st);
+  return integrate<false>(s, precision, b, n, ctx, src, st, act);
 }
 
 int launch_rollout_fast(const aeb_scenario& s, const ParamSrc* src, int precision,
