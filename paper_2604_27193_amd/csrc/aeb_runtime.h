@@ -125,9 +125,33 @@ size_t reduce_scratch_bytes(int64_t n, const aeb_reduce_req& req);
 size_t reduce_scratch_bytes_cap(int cap_sets, int64_t cap_samples, const aeb_reduce_req& req);
 int reduce_enqueue(const OutCols& out, int64_t n, const aeb_reduce_req& req, void* scratch_base,
                    aeb_stats* host_out, hipStream_t stream);
-int reduce_fallback(const OutCols& out, int64_t n, const aeb_reduce_req& req, void* scratch_base,
-                    aeb_stats* dstats, aeb_stats* host_out, hipStream_t stream);
-// reduce_fallback calls since the library was loaded
+// (one set that asks for it: its columns, scratch and statistics)
+struct Fallback {
+  OutCols out;
+  int64_t n;
+  void* scratch;
+  aeb_stats* dstats;  // device
+  aeb_stats* host;
+};
+int reduce_fallback(const Fallback* sets, int count, const aeb_reduce_req& req,
+                    hipStream_t stream);
+// Sets that ask for it, gathered and run FALLBACK_SETS at a time (the sets one
+// launch sequence takes; no allocation).
+constexpr int FALLBACK_SETS = 16;
+struct FallbackList {
+  Fallback f[FALLBACK_SETS];
+  int count = 0;
+  int run(const aeb_reduce_req& req, hipStream_t stream) {
+    const int rc = count > 0 ? reduce_fallback(f, count, req, stream) : AEB_OK;
+    count = 0;
+    return rc;
+  }
+  int add(const Fallback& x, const aeb_reduce_req& req, hipStream_t stream) {
+    f[count++] = x;
+    return count == FALLBACK_SETS ? run(req, stream) : AEB_OK;
+  }
+};
+// sets that took reduce_fallback since the library was loaded
 unsigned long long reduce_fallback_count();
 
 // The reduction of nseg output sets as one launch sequence (every kernel of

@@ -392,30 +392,32 @@ int aeb_graph_finish(aeb_graph* g, void* stream) {
   if (g->mix) {
     if (!g->shape.reduce) return AEB_OK;
     aeb_stats* dst = reduce_table_stats_cap(g->mb.drtab, g->shape.cap_scn, g->shape.cap_total);
+    FallbackList fb;
     for (int j = 0; j < g->last_n; ++j) {
       aeb_stats& s = g->mb.hstats[j];
-      if (s.reserved) {
-        const int rc = reduce_fallback(g->outs[j], g->ns[j], g->shape.req,
-                                       g->red_base + g->red_off[j], dst + j, &s, st);
-        if (rc != AEB_OK) return rc;
-      }
-      s.reserved = 0;
-      g->last_stats[j] = s;
+      if (!s.reserved) continue;
+      const int rc = fb.add(
+          Fallback{g->outs[j], g->ns[j], g->red_base + g->red_off[j], dst + j, &s},
+          g->shape.req, st);
+      if (rc != AEB_OK) return rc;
     }
+    const int rc = fb.run(g->shape.req, st);
+    if (rc != AEB_OK) return rc;
+    for (int j = 0; j < g->last_n; ++j) g->last_stats[j] = g->mb.hstats[j];
     g->last_n = 0;
     return AEB_OK;
   }
   if (!g->reduce) return AEB_OK;
+  FallbackList fb;
   for (size_t j = 0; j < g->outs.size(); ++j) {
     aeb_stats& s = g->host_stats[j];
-    if (s.reserved) {
-      const int rc = reduce_fallback(g->outs[j], g->ns[j], g->req, g->scratch + g->red_off[j],
-                                     set_stats(g, j), &s, st);
-      if (rc != AEB_OK) return rc;
-    }
-    s.reserved = 0;
+    if (!s.reserved) continue;
+    const int rc = fb.add(Fallback{g->outs[j], g->ns[j], g->scratch + g->red_off[j],
+                                   set_stats(g, j), &s},
+                          g->req, st);
+    if (rc != AEB_OK) return rc;
   }
-  return AEB_OK;
+  return fb.run(g->req, st);
 }
 
 int aeb_graph_destroy(aeb_graph* g) {

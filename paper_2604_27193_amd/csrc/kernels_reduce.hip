@@ -63,9 +63,6 @@ struct Sel {
 struct SelState {
   unsigned long long prefix[MAX_T];
   unsigned long long rank[MAX_T];
-  int kind[MAX_T];
-  int count;
-  int pad;
 };
 
 __host__ __device__ inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
@@ -311,11 +308,6 @@ struct MaxOp {
   template <typename T>
   __device__ static T ident() { return -INFINITY; }
 };
-
-__global__ void k_zero_u32(unsigned* p, long long n) {
-  long long i = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0u;
-}
 
 __device__ inline void combine(Partial& a, const Partial& b) {
   a.ncol += b.ncol;
@@ -1112,62 +1104,122 @@ __global__ __launch_bounds__(EB) void k_small_select(RSegs S, RReq rq) {
 }
 
 // ---- fallback: most-significant-digit radix select, 8 passes of 8 bits ----
-__global__ __launch_bounds__(RB) void k_select_hist(OutCols o, long long n, long long chunk,
-                                                    const SelState* ss, int pass, unsigned* ghist) {
+// The sets whose selection asks for it, FB_SETS of them per launch sequence
+// (by value in the kernel arguments): every kernel covers all of them, so a
+// batch with many such sets costs one sequence of 18 short launches and not
+// one per set.  26 sets of 100,000 samples (a sweep's scenarios in which most
+// samples collide share one margin bin): 0.35 ms against 20 ms one set after the
+// other with two wavefronts per SIMD at work on one of 36.
+constexpr int FB_SETS = FALLBACK_SETS;
+struct FbSet {
+  const double* dist;
+  const uint8_t* status;
+  const double* margin;
+  long long n;
+  SelState* ss;
+  unsigned* hist;  // T x 256 counters
+  aeb_stats* st;
+};
+struct FbSets {
+  FbSet s[FB_SETS];
+};
+
+// a set's targets, and its counters cleared
+__global__ __launch_bounds__(RB) void k_select_init(FbSets F, RReq rq) {
+  const FbSet& g = F.s[blockIdx.x];
+  const int T = rq.n_risk + rq.n_mq;
+  for (int j = threadIdx.x; j < T * 256; j += RB) g.hist[j] = 0;
+  if (static_cast<int>(threadIdx.x) < T) {
+    g.ss->prefix[threadIdx.x] = 0;
+    g.ss->rank[threadIdx.x] = sel_rank(rq, g.n, threadIdx.x);
+  }
+}
+
+// Digit counts of the elements that share each target's prefix, a workgroup
+// per EB x CP elements of a set (blockIdx.y), counted in LDS.
+__global__ __launch_bounds__(EB) void k_select_hist(FbSets F, RReq rq, int pass) {
+  const FbSet& g = F.s[blockIdx.y];
+  const long long lo = static_cast<long long>(blockIdx.x) * (EB * CP);
+  if (lo >= g.n) return;
+  const int T = rq.n_risk + rq.n_mq;
   __shared__ unsigned hist[MAX_T * 256];
   __shared__ unsigned long long pre[MAX_T];
-  __shared__ int kind[MAX_T];
-  const int T = ss->count;
-  for (int j = threadIdx.x; j < T * 256; j += RB) hist[j] = 0;
-  if (static_cast<int>(threadIdx.x) < T) {
-    pre[threadIdx.x] = ss->prefix[threadIdx.x];
-    kind[threadIdx.x] = ss->kind[threadIdx.x];
-  }
+  for (int j = threadIdx.x; j < T * 256; j += EB) hist[j] = 0;
+  if (static_cast<int>(threadIdx.x) < T) pre[threadIdx.x] = g.ss->prefix[threadIdx.x];
   __syncthreads();
   const int shift = 56 - 8 * pass;
   const unsigned long long mask = pass == 0 ? 0ull : (~0ull << (64 - 8 * pass));
-  const long long lo = static_cast<long long>(blockIdx.x) * chunk;
-  const long long hi = lo + chunk < n ? lo + chunk : n;
-  for (long long i = lo + threadIdx.x; i < hi; i += RB) {
-    const unsigned long long kd = ordered(censored(o.dist, o.status, i));
-    const unsigned long long km = ordered(o.margin[i]);
+  unsigned long long kd[CP], km[CP];
+#pragma unroll
+  for (int p = 0; p < CP; ++p) {
+    const long long i = lo + p * EB + threadIdx.x;
+    kd[p] = km[p] = 0;
+    if (i < g.n) {
+      kd[p] = ordered(censored(g.dist, g.status, i));
+      km[p] = ordered(g.margin[i]);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < CP; ++p) {
+    const bool ok = lo + p * EB + threadIdx.x < g.n;
     for (int t = 0; t < T; ++t) {
-      const unsigned long long key = kind[t] ? km : kd;
-      if ((key & mask) == (pre[t] & mask))
-        atomicAdd(&hist[t * 256 + static_cast<int>((key >> shift) & 255ull)], 1u);
+      const unsigned long long key = t >= rq.n_risk ? km[p] : kd[p];
+      const bool mine = ok && (key & mask) == (pre[t] & mask);
+      const unsigned d = static_cast<unsigned>((key >> shift) & 255ull);
+      // the leading digits agree over most wavefronts: one add for all of them
+      const unsigned long long who = __ballot(mine);
+      if (who == 0) continue;
+      const unsigned d0 = __shfl(d, __ffsll(static_cast<long long>(who)) - 1);
+      if (__ballot(mine && d != d0) == 0) {
+        if ((threadIdx.x & 63) == 0) atomicAdd(&hist[t * 256 + d0], __popcll(who));
+      } else if (mine) {
+        atomicAdd(&hist[t * 256 + d], 1u);
+      }
     }
   }
   __syncthreads();
-  for (int j = threadIdx.x; j < T * 256; j += RB)
-    if (hist[j]) atomicAdd(&ghist[j], hist[j]);
+  for (int j = threadIdx.x; j < T * 256; j += EB)
+    if (hist[j]) atomicAdd(&g.hist[j], hist[j]);
 }
 
-__global__ void k_select_step(SelState* ss, int pass, unsigned* ghist) {
-  const int t = threadIdx.x;
-  if (t >= ss->count) return;
-  unsigned* h = ghist + t * 256;
-  unsigned long long r = ss->rank[t];
-  int d = 0;
-  for (; d < 255; ++d) {
-    if (r < h[d]) break;
-    r -= h[d];
+// Each target's digit: one wavefront per target, four digits per lane; the
+// counters are cleared for the next pass.  After the last one the prefix is
+// the element.
+__global__ __launch_bounds__(64) void k_select_step(FbSets F, RReq rq, int pass) {
+  const FbSet& g = F.s[blockIdx.y];
+  const int t = blockIdx.x, l = threadIdx.x;
+  unsigned* h = g.hist + t * 256;
+  unsigned long long c[4], tot = 0;
+  for (int q = 0; q < 4; ++q) {
+    c[q] = h[4 * l + q];
+    tot += c[q];
+    h[4 * l + q] = 0;
   }
-  ss->rank[t] = r;
-  ss->prefix[t] |= static_cast<unsigned long long>(d) << (56 - 8 * pass);
-  for (int j = 0; j < 256; ++j) h[j] = 0;
+  unsigned long long inc = tot;  // inclusive scan over the lanes
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned long long v = __shfl_up(inc, o);
+    if (l >= o) inc += v;
+  }
+  const unsigned long long r = g.ss->rank[t];
+  unsigned long long before = inc - tot;
+  if (!(r >= before && r < inc)) return;  // the one lane that holds the rank
+  for (int q = 0; q < 4; ++q) {
+    if (r < before + c[q]) {
+      const unsigned long long pre =
+          g.ss->prefix[t] | (static_cast<unsigned long long>(4 * l + q) << (56 - 8 * pass));
+      g.ss->rank[t] = r - before;
+      g.ss->prefix[t] = pre;
+      if (pass == 7) {
+        if (t < rq.n_risk)
+          g.st->headway[t] = unordered(pre);
+        else
+          g.st->margin_q[t - rq.n_risk] = unordered(pre);
+      }
+      break;
+    }
+    before += c[q];
+  }
 }
-
-__global__ void k_select_out(const SelState* ss, int n_risk, aeb_stats* st) {
-  const int t = threadIdx.x;
-  if (t >= ss->count) return;
-  const double v = unordered(ss->prefix[t]);
-  if (t < n_risk)
-    st->headway[t] = v;
-  else
-    st->margin_q[t - n_risk] = v;
-}
-
-
 
 }  // namespace
 
@@ -1435,44 +1487,43 @@ static std::atomic<unsigned long long> g_fallbacks{0};
 
 unsigned long long reduce_fallback_count() { return g_fallbacks.load(); }
 
-int reduce_fallback(const OutCols& out, int64_t n, const aeb_reduce_req& req, void* scratch_base,
-                    aeb_stats* dstats, aeb_stats* host_out, hipStream_t st) {
-  // a target's value bin held more than CAP candidates: radix select
-  g_fallbacks.fetch_add(1);
-  const RLayout L = layout(n, n_targets(req));
-  const int T = L.T;
-  char* base = static_cast<char*>(scratch_base);
-  SelState* ss = reinterpret_cast<SelState*>(base + L.off_ss);
-  unsigned* shist = reinterpret_cast<unsigned*>(base + L.off_sh);
-  SelState rs;
-  std::memset(&rs, 0, sizeof(rs));
-  rs.count = T;
-  for (int j = 0; j < req.n_risk; ++j) {
-    long long m = static_cast<long long>(std::floor(req.risk[j] * static_cast<double>(n)));
-    rs.rank[j] = static_cast<unsigned long long>(n - m - 1);
-    rs.kind[j] = 0;
+int reduce_fallback(const Fallback* f, int count, const aeb_reduce_req& req, hipStream_t st) {
+  // targets whose value bin held more than CAP candidates: radix select
+  g_fallbacks.fetch_add(static_cast<unsigned long long>(count));
+  const RReq q = rreq_of(req);
+  const int T = n_targets(req);
+  for (int j0 = 0; j0 < count; j0 += FB_SETS) {
+    const int c = count - j0 < FB_SETS ? count - j0 : FB_SETS;
+    FbSets F;
+    std::memset(&F, 0, sizeof(F));
+    int64_t max_n = 0;
+    for (int j = 0; j < c; ++j) {
+      const Fallback& a = f[j0 + j];
+      const RLayout L = layout(a.n, T);
+      char* base = static_cast<char*>(a.scratch);
+      F.s[j] = FbSet{a.out.dist, a.out.status, a.out.margin, a.n,
+                     reinterpret_cast<SelState*>(base + L.off_ss),
+                     reinterpret_cast<unsigned*>(base + L.off_sh), a.dstats};
+      max_n = a.n > max_n ? a.n : max_n;
+    }
+    const unsigned nb = static_cast<unsigned>((max_n + EB * CP - 1) / (EB * CP));
+    hipLaunchKernelGGL(k_select_init, dim3(c), dim3(RB), 0, st, F, q);
+    for (int pass = 0; pass < 8; ++pass) {
+      hipLaunchKernelGGL(k_select_hist, dim3(nb, c), dim3(EB), 0, st, F, q, pass);
+      hipLaunchKernelGGL(k_select_step, dim3(T, c), dim3(64), 0, st, F, q, pass);
+    }
+    AEB_HIP(hipGetLastError());
+    // the order statistics are all that changed
+    for (int j = 0; j < c; ++j) {
+      const Fallback& a = f[j0 + j];
+      AEB_HIP(hipMemcpyAsync(a.host->headway, a.dstats->headway, sizeof(a.host->headway),
+                             hipMemcpyDeviceToHost, st));
+      AEB_HIP(hipMemcpyAsync(a.host->margin_q, a.dstats->margin_q, sizeof(a.host->margin_q),
+                             hipMemcpyDeviceToHost, st));
+    }
   }
-  for (int j = 0; j < req.n_margin_q; ++j) {
-    long long m = static_cast<long long>(std::floor(req.margin_q[j] * static_cast<double>(n)));
-    rs.rank[req.n_risk + j] = static_cast<unsigned long long>(m);
-    rs.kind[req.n_risk + j] = 1;
-  }
-  AEB_HIP(hipMemcpyAsync(ss, &rs, sizeof(rs), hipMemcpyHostToDevice, st));
-  hipLaunchKernelGGL(k_zero_u32, dim3((T * 256 + 255) / 256), dim3(256), 0, st, shist,
-                     static_cast<long long>(T * 256));
-  // larger slices than the main passes: each block merges T x 256 counters
-  const long long fchunk = 16384;
-  const unsigned fnb = static_cast<unsigned>((n + fchunk - 1) / fchunk);
-  for (int pass = 0; pass < 8; ++pass) {
-    hipLaunchKernelGGL(k_select_hist, dim3(fnb), dim3(RB), 0, st, out, static_cast<long long>(n),
-                       fchunk, ss, pass, shist);
-    hipLaunchKernelGGL(k_select_step, dim3(1), dim3(64), 0, st, ss, pass, shist);
-  }
-  hipLaunchKernelGGL(k_select_out, dim3(1), dim3(64), 0, st, ss, req.n_risk, dstats);
-  AEB_HIP(hipGetLastError());
-  AEB_HIP(hipMemcpyAsync(host_out, dstats, sizeof(aeb_stats), hipMemcpyDeviceToHost, st));
   AEB_HIP(hipStreamSynchronize(st));
-  host_out->reserved = 0;
+  for (int j = 0; j < count; ++j) f[j].host->reserved = 0;
   return AEB_OK;
 }
 
@@ -1486,7 +1537,8 @@ int launch_reduce(const OutCols& out, int64_t n, const aeb_reduce_req& req, aeb_
   const int fallback = host_out->reserved;
   host_out->reserved = 0;
   if (!fallback) return AEB_OK;
-  return reduce_fallback(out, n, req, base, static_cast<aeb_stats*>(base), host_out, st);
+  const Fallback f{out, n, base, static_cast<aeb_stats*>(base), host_out};
+  return reduce_fallback(&f, 1, req, st);
 }
 
 int launch_batch_reduce(const OutCols* outs, const int64_t* ns, int nseg,
@@ -1537,14 +1589,15 @@ int launch_batch_reduce(const OutCols* outs, const int64_t* ns, int nseg,
     if (rc != AEB_OK) return rc;
     AEB_HIP(hipStreamSynchronize(st));
     aeb_stats* dst = reduce_table_stats(pool, c, ns + a);
+    FallbackList fb;
     for (int j = 0; j < c; ++j) {
       aeb_stats& h = host_out[a + j];
-      const int fallback = h.reserved;
-      h.reserved = 0;
-      if (!fallback) continue;
-      rc = reduce_fallback(outs[a + j], ns[a + j], req, bases[j], dst + j, &h, st);
+      if (!h.reserved) continue;
+      rc = fb.add(Fallback{outs[a + j], ns[a + j], bases[j], dst + j, &h}, req, st);
       if (rc != AEB_OK) return rc;
     }
+    rc = fb.run(req, st);
+    if (rc != AEB_OK) return rc;
   }
   return AEB_OK;
 }

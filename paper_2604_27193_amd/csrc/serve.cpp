@@ -266,25 +266,33 @@ class HipExecutor final : public serve::Executor {
   void finish(int stream, const std::vector<serve::Request*>& tick) override {
     StreamCtx& S = streams_[stream];
     const int n = static_cast<int>(tick.size());
+    FallbackList fb;
+    int rc = AEB_OK;  // of the fallbacks: a failure is every waiting request's of its group
     for (int j = 0; j < n; ++j) {
       serve::Request* r = tick[j];
       if (S.status != hipSuccess) {
         r->rc = fail(AEB_EDEVICE, std::string("serving launch: ") + hipGetErrorString(S.status));
         continue;
       }
-      aeb_stats& st = S.stats[j];
-      if (st.reserved) {
+      if (S.stats[j].reserved && rc == AEB_OK) {
         // rare: a selection bin too crowded for the in-LDS sort
         char* base = req_base_ + r->off;
         char* red = base + out_bytes(r->scn.n_samples);
         aeb_stats* dst =
             S.last_recorded ? reduce_table_stats_cap(S.rtab, S.last.cap_scn, S.last.cap_total) + j
                             : reduce_table_stats(S.rtab, n, S.ns.data()) + j;
-        r->rc = reduce_fallback(out_cols(base, r->scn.n_samples), r->scn.n_samples, cfg_.req,
-                                red, dst, &st, S.st);
+        rc = fb.add(Fallback{out_cols(base, r->scn.n_samples), r->scn.n_samples, red, dst,
+                             &S.stats[j]},
+                    cfg_.req, S.st);
       }
-      st.reserved = 0;
-      r->stats = st;
+    }
+    if (rc == AEB_OK) rc = fb.run(cfg_.req, S.st);
+    for (int j = 0; j < n; ++j) {
+      serve::Request* r = tick[j];
+      if (S.status != hipSuccess) continue;
+      if (S.stats[j].reserved) r->rc = rc;  // not recomputed
+      S.stats[j].reserved = 0;
+      r->stats = S.stats[j];
     }
   }
 
