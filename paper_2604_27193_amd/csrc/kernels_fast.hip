@@ -27,6 +27,7 @@
 //     atomic counter until none are left (longest first, dynamically balanced).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
 #include <vector>
 
 #include "aeb_common.h"
@@ -255,6 +256,18 @@ HOT uint32_t prep_sample(const PrepArgs& a, int64_t i, uint32_t j, int64_t local
   const uint32_t fine =
       a.nds ? (((ud >> 3) & 7u) << 3) | ((static_cast<uint32_t>(ndl) >> 4) & 7u) : ud & 63u;
   uint32_t key = (limited ? 0u : 4096u) | (ud & ~63u) | fine;
+  // with a lead vehicle: first how far into the run the ego gets out of its
+  // reach, in eighths (a wavefront drops the lead once it is out of reach of
+  // all its lanes): the lead brakes at once, the ego after the dead time and
+  // the actuator's lag, and then gains by what it brakes harder; the last
+  // eighth holds those that never do
+  if (s.obstacle == AEB_OBS_LEAD && !a.ctl) {
+    const float al = static_cast<float>(lead), lag = td + static_cast<float>(tau);
+    const float gain = -static_cast<float>(fmax(s.a_cmd, k.alim) - k.c) - al;
+    const float part = gain > 0.0f ? (lag + al * lag / gain) / t : 1.0f;
+    const uint32_t e = part < 0.875f ? static_cast<uint32_t>(fmaxf(part, 0.0f) * 8.0f) : 7u;
+    key = ((7u - e) << 10) | (limited ? 0u : 512u) | (ud >> 3);
+  }
   // with the controller: first the tick of the predicted full-braking
   // decision (modulo 64, latest first), so a wavefront's lanes reach the
   // thresholds, where the noise can decide and the whole wavefront draws
@@ -845,6 +858,8 @@ struct Wave64 {
   // inside a block (both still to be replayed); friction-limited for good;
   // never limited; can become limited
   lanes_t active, collided, pend, stopped, clamped, free_lane, limited;
+  // lead vehicle: lanes within the bounds of out_of_reach; lanes whose lead was dropped
+  lanes_t tame, dropped;
 };
 
 // Block start states, kept in LDS for the replays.  Slot 0: the start of the
@@ -899,13 +914,14 @@ HOT void keep_start(Saves64<OBS>& S, int slot, int k, int B) {
 // (it may have moved back since): the replay of its block tests every step.
 // With a lead vehicle a lane below zero clearance was reached before any stop
 // in the block, since after a stop the clearance only grows.
-template <int OBS>
+// (DROP: the lead no longer matters, see out_of_reach)
+template <int OBS, bool DROP>
 HOT void block_events(Wave64& L, Saves64<OBS>& S, const Job& J, int k, int B, int impact_exit) {
   constexpr bool LEAD = OBS == AEB_OBS_LEAD;
   lanes_t stop = ballot(L.s.v <= 0.0) & L.active;
   lanes_t hit = 0;
   if (OBS == AEB_OBS_STATIONARY) hit = ballot(L.s.x > J.gap) & L.active & ~stop & ~L.collided;
-  if (LEAD) {
+  if (LEAD && !DROP) {
     hit = ballot(L.l.gmin < 0.0) & L.active;
     stop &= ~hit;
   }
@@ -958,6 +974,25 @@ HOT lanes_t falling(const Wave64& L, const Job& J, double cmd, double ktdt) {
                 fmax(L.s.a, J.alim) - J.c < -1e-3);
 }
 
+// The lanes that the lead vehicle cannot matter to any more: the ego is slower
+// than the lead and brakes harder than it for the rest of the run, so the
+// clearance only grows until the ego stands, and it is already above its
+// running minimum.  No impact can follow, the margin is final, and the lead's
+// state is not read again.  The ego's brake only falls (fall: the lanes of
+// `falling`) and drag only slows, so its acceleration stays at or below
+// max(a, alim) - c; the lead's is -al until it stands, at which point the
+// slower ego has stopped.  The bounds leave room for rounding: in each step
+// the speed difference grows by at least 1e-12 m/s and the clearance by
+// 1e-9 m, several units in the last place of speeds below 1e3 m/s and
+// positions below 1e6 m (tested once per lane: see `tame` in the kernel).
+HOT lanes_t out_of_reach(const Wave64& L, const Job& J, double al, double dt, lanes_t fall) {
+  const double idt = 1.0 / dt;
+  const double ea = fmax(1e-6, 1e-12 * idt), ev = fmax(1e-6, 1e-9 * idt);
+  return fall & L.tame &
+         ballot(fmax(L.s.a, J.alim) - J.c < -al - ea && L.s.v < L.l.vl - ev &&
+                (J.gap + L.l.xl) - L.s.x > L.l.gmin + 1e-6);
+}
+
 // B steps of one form from step k, in pieces of at most 16 (entries of the
 // actuator table are contiguous over a piece), the actuator taken over from the
 // table at the end so that tests, saves and checked steps find it in the lane.
@@ -980,10 +1015,10 @@ HOT void steps64(Wave64& L, const Job& J, double al, double dt, double cmd, int 
 // for every lane when k + B <= wnd).  TOP: a block of the top level, where the
 // steady forms are the runs' business and only the dead time and the generic
 // form are left.
-template <int OBS, int B, int INTEG, bool CTL, bool TOP, bool TAB>
+template <int OBS, int B, int INTEG, bool CTL, bool TOP, bool TAB, bool DROP>
 HOT void run_block64(Wave64& L, Saves64<OBS>& S, const Job& J, double al, const LaneScn& c, int k,
                      int wnd, int impact_exit, double a_warn, double& xmax, const ActTab& at) {
-  constexpr bool LEAD = OBS == AEB_OBS_LEAD;
+  constexpr bool LEAD = OBS == AEB_OBS_LEAD && !DROP;
   const double cmd = lane_cmd<CTL>(L, c, a_warn, k);
   save_start<OBS>(L, S);
   if (k + B <= wnd) {
@@ -996,7 +1031,7 @@ HOT void run_block64(Wave64& L, Saves64<OBS>& S, const Job& J, double al, const 
     steps64<FORM_G, B, LEAD, INTEG, TAB>(L, J, al, c.dt, cmd, k, at);
     L.clamped |= L.limited & ballot(k + B > first_cmd<CTL>(L, c) && L.s.a <= J.alim);
   }
-  block_events<OBS>(L, S, J, k, B, impact_exit);
+  block_events<OBS, DROP>(L, S, J, k, B, impact_exit);
   if (INTEG == AEB_RK4) xmax = fmax(xmax, in(L.active) ? L.s.x : xmax);
 }
 
@@ -1014,11 +1049,11 @@ HOT bool long_block(const Wave64& L, double thr, lanes_t fall) {
 // limited for good, or every one never limited), until the block limit wl or
 // until shorter blocks are the better choice.  Returns the step index after
 // the last block.
-template <int OBS, int K, int FORM, int INTEG, bool TAB>
+template <int OBS, int K, int FORM, int INTEG, bool TAB, bool DROP>
 HOT int run_steady(Wave64& L, Saves64<OBS>& S, const Job& J, double al, double dt, double cmd,
                    int k, int wl, double thr, lanes_t fall, int impact_exit, double& xmax,
-                   const ActTab& at) {
-  constexpr bool LEAD = OBS == AEB_OBS_LEAD;
+                   const ActTab& at, bool may_drop) {
+  constexpr bool LEAD = OBS == AEB_OBS_LEAD && !DROP;
   bool more;
   do {
     k = __builtin_amdgcn_readfirstlane(k);
@@ -1034,10 +1069,12 @@ HOT int run_steady(Wave64& L, Saves64<OBS>& S, const Job& J, double al, double d
     }
     if (K % 16 != 0) block64<FORM, K % 16, LEAD, INTEG>(L.s, L.l, J, al, dt, cmd);
     static_assert(!TAB || K % 16 == 0, "whole pieces");
-    block_events<OBS>(L, S, J, k, K, impact_exit);
+    block_events<OBS, DROP>(L, S, J, k, K, impact_exit);
     if (INTEG == AEB_RK4) xmax = fmax(xmax, in(L.active) ? L.s.x : xmax);
     k += K;
     more = k + K <= wl && L.active != 0 && long_block(L, thr, fall);
+    if (LEAD && may_drop)  // every lane out of the lead's reach: the caller drops it
+      more = more && (L.active & ~out_of_reach(L, J, al, dt, fall)) != 0;
   } while (more);
   return k;
 }
@@ -1106,7 +1143,11 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
     L.l = Ld64{0.0, LEAD ? J.v0 : 0.0, J.gap};
     L.margin = J.gap;
     L.active = ballot(valid);
-    L.collided = L.pend = L.stopped = L.clamped = 0;
+    L.collided = L.pend = L.stopped = L.clamped = L.dropped = 0;
+    // (the horizon in seconds bounds both vehicles' travel)
+    L.tame = LEAD ? ballot(al >= 0.0 && fabs(J.v0) < 1e3 && fabs(J.gap) < 1e5 &&
+                           fabs(J.v0) * (c.nmax * c.dt) < 5e5)
+                  : 0;
     // never limited: a >= a_cmd - (rounding) > alim, so max(a, alim) = a; and
     // limited for good once a <= alim: a never climbs above max(a, a_cmd) <
     // alim.  Both need an actuator that approaches its command from one side,
@@ -1127,6 +1168,29 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
     // controller: the next decision step and the decisions taken (uniform)
     int ktick = 0;
     uint32_t tick = 0;
+    // a run of steady blocks, and one block of a level; with a lead vehicle in
+    // two forms, with it and without
+    auto run = [&](auto form, bool dropped, double cmd, int kk, int lim, lanes_t f) {
+      constexpr int FORM = decltype(form)::value;
+      if (LEAD && dropped)
+        return run_steady<OBS, K, FORM, INTEG, TAB, LEAD>(L, sav, J, al, c.dt, cmd, kk, lim,
+                                                          thr_k, f, ctx.impact_exit, xmax, at,
+                                                          false);
+      // (past the command of every lane, so a lane's speed falls for good)
+      return run_steady<OBS, K, FORM, INTEG, TAB, false>(
+          L, sav, J, al, c.dt, cmd, kk, lim, thr_k, f, ctx.impact_exit, xmax, at,
+          !CTL && (L.active & ~ballot(kk >= c.nd)) == 0);
+    };
+    auto block = [&](auto len, auto top, bool dropped, int kk) {
+      constexpr int B = decltype(len)::value;
+      constexpr bool TOP = decltype(top)::value;
+      if (LEAD && dropped)
+        run_block64<OBS, B, INTEG, CTL, TOP, TAB, LEAD>(L, sav, J, al, c, kk, wnd,
+                                                        ctx.impact_exit, ctx.ca.a_warn, xmax, at);
+      else
+        run_block64<OBS, B, INTEG, CTL, TOP, TAB, false>(
+            L, sav, J, al, c, kk, wnd, ctx.impact_exit, ctx.ca.a_warn, xmax, at);
+    };
     // every lane has ended by its step nmax (the horizon test fires at k + 1 == nmax)
     while (L.active) {
       // the step index is the same in every lane: keep it (and the branches on it) scalar
@@ -1177,6 +1241,13 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
       lanes_t fall = ~0ull;
       if (ballot(L.s.v <= thr_k) & L.active)
         fall = falling(L, J, lane_cmd<CTL>(L, c, ctx.ca.a_warn, k), ktdt);
+      // every lane out of the lead's reach (past the command): drop the lead
+      if (LEAD && !CTL && L.dropped == 0 && k >= wnd) {
+        const double cmd = lane_cmd<CTL>(L, c, ctx.ca.a_warn, k);
+        const lanes_t f = falling(L, J, cmd, ktdt) & ballot(k >= c.nd);
+        if ((L.active & ~out_of_reach(L, J, al, c.dt, f)) == 0) L.dropped = L.active;
+      }
+      const bool drop = LEAD && L.dropped != 0;
       if (k + K <= wl && long_block(L, thr_k, fall)) {
         // past every lane's dead time, in a form no later block changes:
         // a run of blocks without the per-block bookkeeping
@@ -1185,35 +1256,28 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
           // (a clamped lane's speed falls whenever its acceleration without
           // drag is below zero)
           const lanes_t f = ballot(J.nkd <= 0.0 && J.alim - J.c < -1e-3);
-          k = run_steady<OBS, K, FORM_C, INTEG, TAB>(L, sav, J, al, c.dt, 0.0, k, wl, thr_k, f,
-                                                ctx.impact_exit, xmax, at);
+          k = run(std::integral_constant<int, FORM_C>(), drop, 0.0, k, wl, f);
         } else if (past && (L.active & ~L.free_lane) == 0) {
           const double cmd = lane_cmd<CTL>(L, c, ctx.ca.a_warn, k);
           const lanes_t f = falling(L, J, cmd, ktdt);
-          k = run_steady<OBS, K, FORM_F, INTEG, TAB>(L, sav, J, al, c.dt, cmd, k, wl, thr_k, f,
-                                                ctx.impact_exit, xmax, at);
+          k = run(std::integral_constant<int, FORM_F>(), drop, cmd, k, wl, f);
         } else if (past && (L.active & ~(L.clamped | L.free_lane)) == 0) {
           // both kinds: the generic form, whose step serves either
           const double cmd = lane_cmd<CTL>(L, c, ctx.ca.a_warn, k);
           const lanes_t f = falling(L, J, cmd, ktdt);
-          k = run_steady<OBS, K, FORM_G, INTEG, TAB>(L, sav, J, al, c.dt, cmd, k, wl, thr_k, f,
-                                                ctx.impact_exit, xmax, at);
+          k = run(std::integral_constant<int, FORM_G>(), drop, cmd, k, wl, f);
         } else {
-          run_block64<OBS, K, INTEG, CTL, true, TAB>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
-                                          ctx.ca.a_warn, xmax, at);
+          block(std::integral_constant<int, K>(), std::true_type(), drop, k);
           k += K;
         }
       } else if (KM > KS && k + KM <= wl && (ballot(L.s.v <= thr_m) & L.active & ~fall) == 0) {
-        run_block64<OBS, KM, INTEG, CTL, false, TAB>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
-                                         ctx.ca.a_warn, xmax, at);
+        block(std::integral_constant<int, KM>(), std::false_type(), drop, k);
         k += KM;
       } else if (k + KS <= wl && (ballot(L.s.v <= thr_s) & L.active & ~fall) == 0) {
-        run_block64<OBS, KS, INTEG, CTL, false, TAB>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
-                                         ctx.ca.a_warn, xmax, at);
+        block(std::integral_constant<int, KS>(), std::false_type(), drop, k);
         k += KS;
       } else if (K2 < KS && k + K2 <= wl && (ballot(L.s.v <= thr_2) & L.active & ~fall) == 0) {
-        run_block64<OBS, K2, INTEG, CTL, false, TAB>(L, sav, J, al, c, k, wnd, ctx.impact_exit,
-                                         ctx.ca.a_warn, xmax, at);
+        block(std::integral_constant<int, K2>(), std::false_type(), drop, k);
         k += K2;
       } else {
         // checked single steps, in a loop of their own for as long as no
@@ -1224,10 +1288,15 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
           const double cmd = lane_cmd<CTL>(L, c, ctx.ca.a_warn, k);
           bool clamp = false, impact = false, done = false;
           if (in(L.active)) {
-            step64<LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
+            if (LEAD && drop)
+              step64<false, INTEG>(L.s, L.l, J, al, c.dt, cmd);
+            else
+              step64<LEAD, INTEG>(L.s, L.l, J, al, c.dt, cmd);
             if (INTEG == AEB_RK4) xmax = fmax(xmax, L.s.x);
             clamp = k >= first_cmd<CTL>(L, c) && L.s.a <= J.alim;
-            if (LEAD) {
+            if (LEAD && drop) {
+              // no impact can follow
+            } else if (LEAD) {
               const double gk = (J.gap + L.l.xl) - L.s.x;
               L.l.gmin = fmin(L.l.gmin, gk);
               impact = gk < 0.0;
@@ -1281,6 +1350,8 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
       }
       // a stopped lane may also have passed the obstacle in the same block
       bool seek = OBS != AEB_OBS_NONE && (!to_stop || !in(L.collided));
+      // a dropped lead is not reached (and its saved state stands still)
+      if (LEAD) seek = !in(L.dropped);
       bool passed = false;
       constexpr int RB = 8;
       if (K > RB) {
@@ -1294,7 +1365,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
             St64 q = r;
             Ld64 ql = rl;
             block64<FORM_G, RB, LEAD, INTEG>(q, ql, J, al, c.dt, cmd);
-            const bool over = LEAD ? ql.gmin < 0.0 : seek && q.x > J.gap;
+            const bool over = seek && (LEAD ? ql.gmin < 0.0 : q.x > J.gap);
             if (over || (to_stop && q.v <= 0.0)) {
               skip = false;
             } else {
@@ -1318,7 +1389,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
           if (LEAD) {
             const double gk = (J.gap + rl.xl) - r.x;
             rl.gmin = fmin(rl.gmin, gk);
-            impact = gk < 0.0;
+            impact = seek && gk < 0.0;
           } else if (OBS == AEB_OBS_STATIONARY) {
             impact = seek && r.x > J.gap;
           }
@@ -2181,8 +2252,7 @@ __device__ inline void step32l(St32& s, Ld32& l, const L32& c, float tk, float a
 }
 
 template <int FORM, int K>
-__device__ inline void block32l(St32& s, Ld32& l, const L32& c, float tk, float al,
-                                bool flush_end) {
+HOT void block32l(St32& s, Ld32& l, const L32& c, float tk, float al, bool flush_end) {
   float ghl = l.G.hi - l.G.lo;
 #pragma unroll
   for (int j = 0; j < K; ++j) {
@@ -2195,41 +2265,130 @@ __device__ inline void block32l(St32& s, Ld32& l, const L32& c, float tk, float 
   }
 }
 
-struct Lane32L {
-  St32 s, sv;
-  Ld32 l, lv;
-  int sk;
-  bool active, pend, clamped, free_lane;
+// Lane state and lane sets (see Wave64; ended: ended inside a block, to be replayed).
+struct Wave32L {
+  St32 s;
+  Ld32 l;
+  lanes_t active, ended, clamped, free_lane, tame, dropped;
 };
 
-template <int B>
-__device__ inline void run_block32l(Lane32L& L, const L32& c, float al, int nd, int k, int wnd) {
-  // a lane that has ended keeps the start state of the block it ended in
-  if (L.active) {
-    L.sv = L.s;
-    L.lv = L.l;
-    L.sk = k;
-  }
-  const float tk = k >= nd ? c.tb : c.td;
-  const bool fl = (k + B) % FLUSH == 0;
-  if (k + B <= wnd) {
-    block32l<FORM_D, B>(L.s, L.l, c, tk, al, fl);
-  } else if (__all(!L.active || L.clamped)) {
-    block32l<FORM_C, B>(L.s, L.l, c, tk, al, fl);
-  } else if (__all(!L.active || L.free_lane)) {
-    block32l<FORM_F, B>(L.s, L.l, c, tk, al, fl);
-  } else {
-    block32l<FORM_G, B>(L.s, L.l, c, tk, al, fl);
-    L.clamped = L.clamped || (k + B > nd && L.s.e + c.tb <= c.alc);
-  }
-  if (L.active && L.l.gmin < 0.0f) {  // the lead was reached inside the block
-    L.pend = true;
-    L.active = false;
+// Block start states in LDS, as Saves64: every lane ends in its last block.
+struct Saves32L {
+  float f[2][12][ROLL_MAX];
+  int k[ROLL_MAX], end[ROLL_MAX];
+};
+
+HOT void save_start32l(const Wave32L& L, Saves32L& S) {
+  const int t = threadIdx.x;
+  S.f[SAV_CUR][0][t] = L.s.vb;
+  S.f[SAV_CUR][1][t] = L.s.vi;
+  S.f[SAV_CUR][2][t] = L.s.e;
+  S.f[SAV_CUR][3][t] = L.s.p;
+  S.f[SAV_CUR][4][t] = L.s.X.hi;
+  S.f[SAV_CUR][5][t] = L.s.X.lo;
+  S.f[SAV_CUR][6][t] = L.l.vb;
+  S.f[SAV_CUR][7][t] = L.l.vi;
+  S.f[SAV_CUR][8][t] = L.l.pg;
+  S.f[SAV_CUR][9][t] = L.l.G.hi;
+  S.f[SAV_CUR][10][t] = L.l.G.lo;
+  S.f[SAV_CUR][11][t] = L.l.gmin;
+}
+
+// The lanes that ended in the block of B steps from step k: reached the lead
+// (its replay finds which came first), or stopped.
+template <bool DROP>
+HOT void block_events32l(Wave32L& L, Saves32L& S, int k, int B) {
+  lanes_t over = ballot(L.s.vb + L.s.vi <= 0.0f) & L.active;
+  if (!DROP) over |= ballot(L.l.gmin < 0.0f) & L.active;
+  L.ended |= over;
+  L.active &= ~over;
+  if (over) {
+    if (in(over)) {
+      const int t = threadIdx.x;
+#pragma unroll
+      for (int q = 0; q < 12; ++q) S.f[SAV_END][q][t] = S.f[SAV_CUR][q][t];
+      S.k[t] = k;
+      S.end[t] = k + B;
+    }
+    lanes_join();
   }
 }
 
+// The lanes out of the lead's reach (see out_of_reach of the FP64 kernel).  The
+// step's rounding is that of the two increments, below 4 * 2^-24 * 64 dt
+// (dmax + al) <= 1.6e-3 dt for the rates `tame` admits, against a gain of at
+// least 1e-2 dt in the speed difference; the clearance is read to a few units in
+// its last place.
+HOT lanes_t out_of_reach32(const Wave32L& L, const L32& c, float tk, float al, lanes_t fall) {
+  const float g = clearance(L.l);
+  return fall & L.tame &
+         ballot(fmaxf(L.s.e + tk, c.alc) < -al - 1e-2f &&
+                L.s.vb + L.s.vi < lead_speed(L.l) - 1e-2f &&
+                g > L.l.gmin + (1e-3f + 1e-6f * fabsf(g)));
+}
+
+// B steps of one form with the lead, or without it (DROP), pieces of 16 with the
+// position's sum pinned at the end of each (see run_steady32)
+template <int FORM, int B, bool DROP>
+HOT void steps32l(Wave32L& L, const L32& c, float tk, float al, bool flush_end) {
+  constexpr int P = B < 16 ? B : 16;
+#pragma unroll
+  for (int q = 0; q < B / P; ++q) {
+    const bool fl = flush_end && q == B / P - 1;
+    if (DROP) {
+      block32<FORM, P, true>(L.s, c, tk);
+      if (fl) flush32(L.s, true);
+    } else {
+      block32l<FORM, P>(L.s, L.l, c, tk, al, fl);
+    }
+    asm volatile("" : "+v"(L.s.p));
+  }
+}
+
+template <int B, bool TOP, bool DROP>
+HOT void run_block32l(Wave32L& L, Saves32L& S, const L32& c, float al, int nd, int k, int wnd) {
+  save_start32l(L, S);
+  const float tk = k >= nd ? c.tb : c.td;
+  const bool fl = (k + B) % FLUSH == 0;
+  if (k + B <= wnd) {
+    steps32l<FORM_D, B, DROP>(L, c, tk, al, fl);
+  } else if (!TOP && (L.active & ~L.clamped) == 0) {
+    steps32l<FORM_C, B, DROP>(L, c, tk, al, fl);
+  } else if (!TOP && (L.active & ~L.free_lane) == 0) {
+    steps32l<FORM_F, B, DROP>(L, c, tk, al, fl);
+  } else {
+    steps32l<FORM_G, B, DROP>(L, c, tk, al, fl);
+    L.clamped |= ballot(k + B > nd && L.s.e + c.tb <= c.alc);
+  }
+  block_events32l<DROP>(L, S, k, B);
+}
+
+HOT bool long_block32l(const Wave32L& L, float thr, lanes_t fall) {
+  const float v = L.s.vb + L.s.vi;
+  const lanes_t low = ballot(v <= thr) & L.active;
+  if (low == 0) return true;
+  return (low & ~fall) == 0 && (ballot(v > 2.0f * thr) & L.active) != 0;
+}
+
+template <int K, int FORM, bool DROP>
+HOT int run_steady32l(Wave32L& L, Saves32L& S, const L32& c, float tk, float al, int k, int wl,
+                      lanes_t fall) {
+  bool more;
+  do {
+    k = __builtin_amdgcn_readfirstlane(k);
+    save_start32l(L, S);
+    steps32l<FORM, K, DROP>(L, c, tk, al, K == FLUSH || (k + K) % FLUSH == 0);
+    block_events32l<DROP>(L, S, k, K);
+    k += K;
+    more = k + K <= wl && L.active != 0 && long_block32l(L, c.thr, fall);
+    if (!DROP)  // every lane out of the lead's reach: the caller drops it
+      more = more && (L.active & ~out_of_reach32(L, c, tk, al, fall)) != 0;
+  } while (more);
+  return k;
+}
+
 template <int K, bool BATCH>
-__global__ __launch_bounds__(256) void k_roll_fp32c_lead(const Job* __restrict__ jobs,
+__global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c_lead(const Job* __restrict__ jobs,
                                                          const LeadJob* __restrict__ leads,
                                                          const uint32_t* __restrict__ perm,
                                                          int64_t n, Ctx ctx, double band_abs,
@@ -2237,10 +2396,12 @@ __global__ __launch_bounds__(256) void k_roll_fp32c_lead(const Job* __restrict__
                                                          unsigned long long* counter,
                                                          int persistent) {
   if (ctx.hdr) n = ctx.hdr->total;  // a recorded mix: its size from the device header
+  // the block ladder of the FP64 kernel, blocks starting on multiples of their length
   constexpr int KS = 4;
   constexpr int KM = K >= 64 ? 16 : KS;  // middle level of the block ladder
   static_assert(FLUSH % K == 0 && K % KM == 0 && KM % KS == 0,
                 "flush points must fall on block ends");
+  __shared__ Saves32L sav;
   for (int pass = 0;; ++pass) {
     const int64_t base = next_chunk(counter, persistent, pass, n);
     if (base >= n) break;
@@ -2254,10 +2415,10 @@ __global__ __launch_bounds__(256) void k_roll_fp32c_lead(const Job* __restrict__
       J = Job{1.0, 0.0, 0.0, -1.0, 0.5, 1e30, 1.0, 0.0f, 0u};
     }
     const float al = valid ? static_cast<float>(leads[g].decel) : 0.0f;
-    const LaneScn sc = lane_scn<BATCH>(ctx, J, valid, g);
+    const LaneScn sc = BATCH ? lane_scn<BATCH>(ctx, J, valid, g)
+                             : lane_values(lane_scn<BATCH>(ctx, J, valid, g));
     const int nd = sc.nd, nmax = sc.nmax;
-    const bool varnd = BATCH || ctx.nds;
-    const int wnd = __builtin_amdgcn_readfirstlane(varnd ? wave_min(valid ? nd : INT_MAX) : nd);
+    const int wnd = __builtin_amdgcn_readfirstlane(wave_min(valid ? nd : INT_MAX));
     L32 c;
     c.dt = static_cast<float>(sc.dt);
     c.nkd = static_cast<float>(J.nkd);
@@ -2272,7 +2433,7 @@ __global__ __launch_bounds__(256) void k_roll_fp32c_lead(const Job* __restrict__
     const float thr_m = static_cast<float>(static_cast<double>(KM) * sc.dt * J.dmax);
     const float thr_s = static_cast<float>(static_cast<double>(KS) * sc.dt * J.dmax);
     const double band = band_abs + band_rel * fabs(J.gap);
-    Lane32L L;
+    Wave32L L;
     L.s.vb = static_cast<float>(J.v0);
     L.s.vi = static_cast<float>(J.v0 - static_cast<double>(L.s.vb));
     L.s.e = 0.0f;
@@ -2283,98 +2444,186 @@ __global__ __launch_bounds__(256) void k_roll_fp32c_lead(const Job* __restrict__
     L.l.G.hi = c.gapf;
     L.l.G.lo = static_cast<float>(static_cast<double>(c.gapf) - J.gap);
     L.l.gmin = clearance(L.l);
-    L.sv = L.s;
-    L.lv = L.l;
-    L.sk = 0;
-    L.active = valid;
-    L.pend = L.clamped = false;
-    L.free_lane = J.alim < sc.a_cmd - 1e-6;
+    L.active = ballot(valid);
+    L.ended = L.clamped = L.dropped = 0;
+    L.free_lane = ballot(J.alim < sc.a_cmd - 1e-6);
+    L.tame = ballot(al >= 0.0f && J.dmax + al < 100.0);
     bool boundary = false, collided = false;
     int end = 0, steps = 0;
     double dist = 0.0;
     float vimp = 0.0f;
-    float gprev = L.l.gmin;
     float gm_end = L.l.gmin;  // running minimum of the clearance when the lane ended
     int k = 0, wl = -1;
-    for (;;) {
+    auto run = [&](auto form, bool drop, float tk, int kk, int lim, lanes_t f) {
+      constexpr int FORM = decltype(form)::value;
+      return drop ? run_steady32l<K, FORM, true>(L, sav, c, tk, al, kk, lim, f)
+                  : run_steady32l<K, FORM, false>(L, sav, c, tk, al, kk, lim, f);
+    };
+    auto block = [&](auto len, auto top, bool drop, int kk) {
+      constexpr int B = decltype(len)::value;
+      constexpr bool TOP = decltype(top)::value;
+      if (drop)
+        run_block32l<B, TOP, true>(L, sav, c, al, nd, kk, wnd);
+      else
+        run_block32l<B, TOP, false>(L, sav, c, al, nd, kk, wnd);
+    };
+    while (L.active) {
       k = __builtin_amdgcn_readfirstlane(k);
-      if (!__any(L.active)) break;
-      if (!varnd || k >= wl) wl = wave_lim(varnd, L.active, k, nd, nmax);
-      if (k == nd) L.s.e += c.ejump;
+      if (k >= wl) wl = wave_lim(true, in(L.active), k, nd, nmax);
+      L.s.e += k == nd ? c.ejump : 0.0f;
       const float v_now = L.s.vb + L.s.vi;
-      if (k % K == 0 && k + K <= wl && !__any(L.active && v_now <= c.thr)) {
-        run_block32l<K>(L, c, al, nd, k, wnd);
-        k += K;
+      const float tk = k >= nd ? c.tb : c.td;
+      lanes_t fall = ~0ull;
+      if (ballot(v_now <= c.thr) & L.active) fall = falling32(L.s, c, tk);
+      // past the command of every lane, each speed that falls does so for good
+      const lanes_t past_nd = ballot(k >= nd);
+      if (L.dropped == 0 && k >= wnd &&
+          (L.active & ~out_of_reach32(L, c, tk, al, falling32(L.s, c, tk) & past_nd)) == 0)
+        L.dropped = L.active;
+      const bool drop = L.dropped != 0;
+      if (k % K == 0 && k + K <= wl && long_block32l(L, c.thr, fall)) {
+        // (see the kernel without a lead)
+        const bool past = k + K > wnd && (L.active & ~past_nd) == 0;
+        const lanes_t f = falling32(L.s, c, tk);
+        if (past && (L.active & ~L.clamped) == 0) {
+          k = run(std::integral_constant<int, FORM_C>(), drop, tk, k, wl, f);
+        } else if (past && (L.active & ~L.free_lane) == 0) {
+          k = run(std::integral_constant<int, FORM_F>(), drop, tk, k, wl, f);
+        } else if (past && (L.active & ~(L.clamped | L.free_lane)) == 0) {
+          k = run(std::integral_constant<int, FORM_G>(), drop, tk, k, wl, f);
+        } else {
+          block(std::integral_constant<int, K>(), std::true_type(), drop, k);
+          k += K;
+        }
       } else if (KM > KS && k % KM == 0 && k + KM <= wl &&
-                 !__any(L.active && v_now <= thr_m)) {
-        run_block32l<KM>(L, c, al, nd, k, wnd);
+                 (ballot(v_now <= thr_m) & L.active & ~fall) == 0) {
+        block(std::integral_constant<int, KM>(), std::false_type(), drop, k);
         k += KM;
-      } else if (k % KS == 0 && k + KS <= wl && !__any(L.active && v_now <= thr_s)) {
-        run_block32l<KS>(L, c, al, nd, k, wnd);
+      } else if (k % KS == 0 && k + KS <= wl &&
+                 (ballot(v_now <= thr_s) & L.active & ~fall) == 0) {
+        block(std::integral_constant<int, KS>(), std::false_type(), drop, k);
         k += KS;
       } else {
-        if (L.active) {
+        bool clamp = false, done = false;
+        if (in(L.active)) {
           const float gp = clearance(L.l);
-          step32l<FORM_G>(L.s, L.l, c, k >= nd ? c.tb : c.td, al);
-          if ((k + 1) % FLUSH == 0) flush32l(L.s, L.l);
-          if (k >= nd) L.clamped = L.clamped || (L.s.e + c.tb <= c.alc);
-          const float gk = clearance(L.l);
-          L.l.gmin = fminf(L.l.gmin, gk);
+          bool impact = false;
+          if (drop) {
+            step32(L.s, c, k >= nd);
+            if ((k + 1) % FLUSH == 0) flush32(L.s, true);
+          } else {
+            step32l<FORM_G>(L.s, L.l, c, tk, al);
+            if ((k + 1) % FLUSH == 0) flush32l(L.s, L.l);
+            const float gk = clearance(L.l);
+            L.l.gmin = fminf(L.l.gmin, gk);
+            impact = gk < 0.0f;
+            if (impact)
+              boundary =
+                  fabs(static_cast<double>(gp)) < band || fabs(static_cast<double>(gk)) < band;
+          }
+          clamp = k >= nd && L.s.e + c.tb <= c.alc;
           const float v = L.s.vb + L.s.vi;
-          if (gk < 0.0f) {
-            L.active = false;
+          if (impact) {
             collided = true;
             vimp = v - lead_speed(L.l);
             end = AEB_END_IMPACT;
-            steps = k + 1;
-            dist = L.s.X.value(L.s.p);
-            boundary = fabs(static_cast<double>(gp)) < band || fabs(static_cast<double>(gk)) < band;
           } else if (v <= 0.0f) {
-            L.active = false;
             end = AEB_END_STOP;
-            steps = k + 1;
-            dist = L.s.X.value(L.s.p);
           } else if (k + 1 == nmax) {
-            L.active = false;
             end = AEB_END_HORIZON;
+          }
+          done = end != 0;
+          if (done) {
             steps = k + 1;
             dist = L.s.X.value(L.s.p);
+            gm_end = L.l.gmin;
           }
-          if (!L.active) gm_end = L.l.gmin;
         }
+        lanes_join();
+        L.clamped |= ballot(clamp);
+        L.active &= ~ballot(done);
         k += 1;
       }
     }
-    // replay the block in which each pending lane reached the lead: the same
-    // steps one at a time, with the clearance read after each (post-flush)
-    if (__any(L.pend)) {
-      St32 r = L.sv;
-      Ld32 rl = L.lv;
-      int kr = L.sk;
-      gprev = clearance(rl);
-      for (int it = 0; it < K; ++it) {
-        if (!__any(L.pend)) break;
-        if (L.pend) {
+    // replay the block in which each ended lane reached the lead or stopped: the
+    // same steps, chunks of RB without either whole, then one at a time with the
+    // clearance read after each (post-flush); a dropped lead is not reached, and
+    // its running minimum stands
+    if (L.ended) {
+      const int t = threadIdx.x;
+      bool go = in(L.ended);
+      const bool seek = !in(L.dropped);
+      St32 r = L.s;
+      Ld32 rl = L.l;
+      int kr = 0, se = 0;
+      if (go) {
+        r.vb = sav.f[SAV_END][0][t];
+        r.vi = sav.f[SAV_END][1][t];
+        r.e = sav.f[SAV_END][2][t];
+        r.p = sav.f[SAV_END][3][t];
+        r.X.hi = sav.f[SAV_END][4][t];
+        r.X.lo = sav.f[SAV_END][5][t];
+        rl.vb = sav.f[SAV_END][6][t];
+        rl.vi = sav.f[SAV_END][7][t];
+        rl.pg = sav.f[SAV_END][8][t];
+        rl.G.hi = sav.f[SAV_END][9][t];
+        rl.G.lo = sav.f[SAV_END][10][t];
+        rl.gmin = sav.f[SAV_END][11][t];
+        kr = sav.k[t];
+        se = sav.end[t];
+        gm_end = rl.gmin;
+      }
+      constexpr int RB = 8;
+      if (K > RB) {
+        const float tk = kr >= nd ? c.tb : c.td;  // one target over a block
+        bool skip = go;
+        for (int it = 0; it < K / RB; ++it) {
+          skip = skip && kr % RB == 0 && kr + RB <= se;
+          if (ballot(skip) == 0) break;
+          if (skip) {
+            St32 q = r;
+            Ld32 ql = rl;
+            block32l<FORM_G, RB>(q, ql, c, tk, al, (kr + RB) % FLUSH == 0);
+            if ((seek && ql.gmin < 0.0f) || q.vb + q.vi <= 0.0f) {
+              skip = false;
+            } else {
+              r = q;
+              rl = ql;
+              kr += RB;
+            }
+          }
+        }
+      }
+      for (int it = 0; it <= K; ++it) {
+        if (ballot(go) == 0) break;
+        if (go) {
+          const float gprev = clearance(rl);
           step32l<FORM_G>(r, rl, c, kr >= nd ? c.tb : c.td, al);
           ++kr;
           if (kr % FLUSH == 0) flush32l(r, rl);
           const float gk = clearance(rl);
           rl.gmin = fminf(rl.gmin, gk);
-          if (gk < 0.0f) {
-            L.pend = false;
+          const float v = r.vb + r.vi;
+          if (seek && gk < 0.0f) {
+            go = false;
             collided = true;
-            vimp = (r.vb + r.vi) - lead_speed(rl);
+            vimp = v - lead_speed(rl);
             end = AEB_END_IMPACT;
+            boundary =
+                fabs(static_cast<double>(gprev)) < band || fabs(static_cast<double>(gk)) < band;
+          } else if (v <= 0.0f) {
+            go = false;
+            end = AEB_END_STOP;
+          }
+          if (!go) {
             steps = kr;
             dist = r.X.value(r.p);
-            boundary = fabs(static_cast<double>(gprev)) < band || fabs(static_cast<double>(gk)) < band;
-            gm_end = rl.gmin;
+            if (seek) gm_end = rl.gmin;
           }
-          gprev = gk;
         }
       }
+      if (go) vimp = __builtin_nanf("");  // unreachable; makes a broken replay visible
     }
-    if (L.pend) vimp = __builtin_nanf("");  // unreachable; makes a broken replay visible
     if (!collided) boundary = static_cast<double>(gm_end) < band;
     if (ctx.lanes) count_lanes(ctx.lanes, k, 64);
     if (valid) {
