@@ -9,6 +9,7 @@ with an error; there is no fallback.
 """
 import ctypes as C
 import os
+import struct
 
 import numpy as np
 
@@ -191,46 +192,55 @@ def _check(rc):
     return rc
 
 
+# The scenario struct packed in one call (a ctypes field at a time it took 35 us,
+# as long as a small launch's kernels): the layout of ``Scenario``, integers as
+# unsigned words so that out-of-range values wrap as in a ctypes field.
+_SCN = struct.Struct("<QQQ4I8d" + 11 * "II4d" + "2dII6dII" + 9 * "II4d")
+assert _SCN.size == C.sizeof(Scenario)
+_PAD = ((0.0,) * 4, (0.0,) * 3, (0.0,) * 2, (0.0,), ())
+_NO_DIST = (0, 0, 0.0, 0.0, 0.0, 0.0)
+_M64, _M32 = 0xFFFFFFFFFFFFFFFF, 0xFFFFFFFF
+
+
 def _dist(spec):
-    d = Dist()
-    d.kind = DIST_KINDS[spec[0]]
-    vals = [float(v) for v in spec[1:]] + [0.0] * (4 - len(spec[1:]))
-    d.p0, d.p1, d.lo, d.hi = vals
-    if spec[0] == "const":
-        d.p1 = 0.0
-    return d
+    kind = DIST_KINDS[spec[0]]
+    if len(spec) > 5:
+        raise ValueError("a distribution has at most four parameters")
+    vals = (*map(float, spec[1:]), *_PAD[len(spec) - 1])
+    if kind == 0:
+        vals = (vals[0], 0.0, vals[2], vals[3])
+    return (kind, 0, *vals)
 
 
 def scenario(d):
     """Marshal a scenario dict (see workloads.py) into ``aeb_scenario``."""
-    s = Scenario()
-    s.seed = int(d["seed"]) & 0xFFFFFFFFFFFFFFFF
-    s.scenario_id = int(d["scenario_id"]) & 0xFFFFFFFFFFFFFFFF
-    s.n_samples = int(d["n_samples"])
-    s.integrator = INTEGRATORS[d["integrator"]]
-    s.obstacle = OBSTACLES[d["obstacle"]]
-    s.impact_exit = int(bool(d.get("impact_exit", False)))
-    s.nofma = int(bool(d.get("nofma", False)))
+    get = d.get
+    v = [int(d["seed"]) & _M64, int(d["scenario_id"]) & _M64, int(d["n_samples"]) & _M64,
+         INTEGRATORS[d["integrator"]], OBSTACLES[d["obstacle"]],
+         int(bool(get("impact_exit", False))), int(bool(get("nofma", False)))]
     for f in ("dt", "horizon", "dead_time", "a_cmd", "g", "rho", "h_cog", "wheelbase"):
-        setattr(s, f, float(d[f]))
+        v.append(float(d[f]))
     for f in DISTS:
-        setattr(s, f, _dist(d[f]))
-    per = dict(PERCEPTION_DEFAULTS)
-    per.update({k: d[k] for k in PERCEPTION_DEFAULTS if k in d})
-    s.latency = _dist(per["latency"])
-    s.occlusion = _dist(per["occlusion"])
-    s.frame_period = float(per["frame_period"])
-    s.p_dropout = float(per["p_dropout"])
-    s.confirm = int(per["confirm"])
+        v += _dist(d[f])
+    per = PERCEPTION_DEFAULTS
+    v += _dist(get("latency", per["latency"]))
+    v += _dist(get("occlusion", per["occlusion"]))
+    v += (float(get("frame_period", per["frame_period"])),
+          float(get("p_dropout", per["p_dropout"])),
+          int(get("confirm", per["confirm"])) & _M32, 0)
     for f in CONTROL_FIELDS:
-        setattr(s, f, float(d.get(f, 0.0)))
+        v.append(float(get(f, 0.0)))
     # importance sampling: {"param": distribution} drawn instead of the nominal
-    mask = 0
-    for name, spec in d.get("proposal", {}).items():
+    mask, proposals = 0, [_NO_DIST] * 9
+    for name, spec in get("proposal", {}).items():
         j = DISTS.index(name)
         mask |= 1 << j
-        s.proposal[j] = _dist(spec)
-    s.is_mask = mask
+        proposals[j] = _dist(spec)
+    v += (mask, 0)
+    for q in proposals:
+        v += q
+    s = Scenario()
+    _SCN.pack_into(s, 0, *v)
     return s
 
 
@@ -364,22 +374,36 @@ def reduce_request(risk=(), margin_q=(), grid=None):
     return req
 
 
+_STATS = np.dtype(Stats)
+_STAT_HEAD = ("n", "n_collide", "n_stop", "n_impact", "n_horizon", "n_boundary", "p_collision",
+              "mean_dist", "sd_dist", "dist_min", "dist_max")
+_STAT_KEYS = _STAT_HEAD + ("headway", "margin_min", "margin_mean", "margin_q", "v_impact_max",
+                           "risk_count", "risk_p", "weighted", "p_collision_w",
+                           "p_collision_se", "weight_mean", "risk_pw", "risk_se")
+
+
+def stats_dicts(st, k, n_risk, n_mq, n_grid):
+    """The first k statistics of an array of ``Stats`` as dicts, taken a field at
+    a time over all of them."""
+    a = np.frombuffer(st, dtype=_STATS, count=k)
+
+    def rows(f, n):
+        return np.ascontiguousarray(a[f][:, :n])
+
+    def copies(f):  # each row its own array
+        return [r.copy() for r in a[f][:, :n_grid]]
+
+    cols = [a[f].tolist() for f in _STAT_HEAD]
+    cols += [rows("headway", n_risk).tolist(), a["margin_min"].tolist(),
+             a["margin_mean"].tolist(), rows("margin_q", n_mq).tolist(),
+             a["v_impact_max"].tolist(), copies("risk_count"), copies("risk_p"),
+             a["weighted"].tolist(), a["p_collision_w"].tolist(), a["p_collision_se"].tolist(),
+             a["weight_mean"].tolist(), copies("risk_pw"), copies("risk_se")]
+    return [dict(zip(_STAT_KEYS, row)) for row in zip(*cols)]
+
+
 def stats_dict(st, n_risk, n_mq, n_grid):
-    return {
-        "n": st.n, "n_collide": st.n_collide, "n_stop": st.n_stop, "n_impact": st.n_impact,
-        "n_horizon": st.n_horizon, "n_boundary": st.n_boundary, "p_collision": st.p_collision,
-        "mean_dist": st.mean_dist,
-        "sd_dist": st.sd_dist, "dist_min": st.dist_min, "dist_max": st.dist_max,
-        "headway": list(st.headway)[:n_risk], "margin_min": st.margin_min,
-        "margin_mean": st.margin_mean, "margin_q": list(st.margin_q)[:n_mq],
-        "v_impact_max": st.v_impact_max,
-        "risk_count": np.array(st.risk_count[:n_grid], dtype=np.int64),
-        "risk_p": np.array(st.risk_p[:n_grid], dtype=np.float64),
-        "weighted": st.weighted, "p_collision_w": st.p_collision_w,
-        "p_collision_se": st.p_collision_se, "weight_mean": st.weight_mean,
-        "risk_pw": np.array(st.risk_pw[:n_grid], dtype=np.float64),
-        "risk_se": np.array(st.risk_se[:n_grid], dtype=np.float64),
-    }
+    return stats_dicts(st, 1, n_risk, n_mq, n_grid)[0]
 
 
 def reduce(out, risk=(), margin_q=(), grid=None, stream=None):
@@ -479,7 +503,7 @@ def batch_reduce(outs, risk=(), margin_q=(), grid=None, stream=None):
     oarr = (Outputs * k)(*[_outputs_struct(o) for o in outs])
     st = (Stats * k)()
     _check(lib().aeb_batch_reduce(oarr, k, C.byref(req), st, _stream(stream)))
-    return [stats_dict(st[j], req.n_risk, req.n_margin_q, req.n_grid) for j in range(k)]
+    return stats_dicts(st, k, req.n_risk, req.n_margin_q, req.n_grid)
 
 
 class Server:
@@ -627,7 +651,7 @@ class Graph:
         if self.req is None:
             return None
         r = self.req
-        st = [stats_dict(self._stats[j], r.n_risk, r.n_margin_q, r.n_grid) for j in range(self.k)]
+        st = stats_dicts(self._stats, self.k, r.n_risk, r.n_margin_q, r.n_grid)
         return st if self.batch else st[0]
 
     def close(self):
@@ -679,7 +703,7 @@ class MixGraph:
         if self.req is None:
             return None
         r = self.req
-        return [stats_dict(self._st[j], r.n_risk, r.n_margin_q, r.n_grid) for j in range(self.k)]
+        return stats_dicts(self._st, self.k, r.n_risk, r.n_margin_q, r.n_grid)
 
     def close(self):
         if getattr(self, "h", None):
