@@ -1926,26 +1926,39 @@ HOT bool long_block32(const Wave32& L, float thr, lanes_t fall) {
   return (low & ~fall) == 0 && (ballot(v > 2.0f * thr) & L.active) != 0;
 }
 
+// K-step pieces of a run between its tests: two, unrolled, for split speeds in a
+// batched launch, whose wavefronts are long and many, so that the tests' share is
+// worth a longer replay of the block with the crossing or the stop (1,000
+// uneven scenarios, most of their steps split: kernel 32.4 -> 30.4 ms); one
+// elsewhere (1,048,576 samples of one scenario 0.575 ms, 0.59 with two;
+// 200,000 0.157 and 0.165).
+template <int K, bool SPLIT, bool BATCH>
+constexpr int run_pieces() { return SPLIT && BATCH && K == FLUSH ? 2 : 1; }
+
 // Consecutive K-step blocks in one steady form, SPLIT if any lane's speed is
 // split (as run_steady of the FP64 kernel), with the flush at every flush
 // point.  (Two blocks per round of tests, the second in a rolled loop: no
 // faster for one wavefront on its SIMD, and 35 more VGPRs.)
-template <int OBS, int K, int FORM, bool SPLIT>
+template <int OBS, int K, int FORM, bool SPLIT, bool BATCH>
 HOT int run_steady32(Wave32& L, Saves32<OBS>& S, const L32& c, float tk, bool split, int k,
                      int wl, lanes_t fall, int impact_exit) {
+  constexpr int U = run_pieces<K, SPLIT, BATCH>();
   bool more;
   do {
     k = __builtin_amdgcn_readfirstlane(k);
     save_start32<OBS>(L, S);
 #pragma unroll
-    for (int q = 0; q < K / 16; ++q) {
-      block32<FORM, 16, SPLIT>(L.s, c, tk);
-      asm volatile("" : "+v"(L.s.p));  // no position update sunk to the end of the run
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int q = 0; q < K / 16; ++q) {
+        block32<FORM, 16, SPLIT>(L.s, c, tk);
+        asm volatile("" : "+v"(L.s.p));  // no position update sunk to the end of the run
+      }
+      if (K == FLUSH || (k + K) % FLUSH == 0) flush32(L.s, SPLIT && split);
     }
-    if (K == FLUSH || (k + K) % FLUSH == 0) flush32(L.s, SPLIT && split);
-    block_events32<OBS>(L, S, c, k, K, impact_exit);
-    k += K;
-    more = k + K <= wl && L.active != 0 && long_block32(L, c.thr, fall);
+    block_events32<OBS>(L, S, c, k, U * K, impact_exit);
+    k += U * K;
+    more = k + U * K <= wl && L.active != 0 && long_block32(L, U * c.thr, fall);
   } while (more);
   return k;
 }
@@ -2028,23 +2041,25 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__
         // past every lane's dead time, in a form no later block changes: a run
         // of blocks
         const lanes_t f = falling32(L.s, c, tk);
-        const bool past = k + K > wnd;
         const bool no_split = (splits & L.active) == 0;
+        constexpr int U = run_pieces<K, true, BATCH>();
+        const bool past = k + K > wnd && (no_split || U == 1 ||
+                                          (k + U * K <= wl && long_block32(L, U * c.thr, f)));
         const bool steady_c = past && (L.active & ~L.clamped) == 0;
         const bool steady_f = past && !steady_c && (L.active & ~L.free_lane) == 0;
         const bool steady_g = past && (L.active & ~(L.clamped | L.free_lane)) == 0;
         if (steady_c && no_split) {
-          k = run_steady32<OBS, K, FORM_C, false>(L, sav, c, tk, split, k, wl, f, impact_exit);
+          k = run_steady32<OBS, K, FORM_C, false, BATCH>(L, sav, c, tk, split, k, wl, f, impact_exit);
         } else if (steady_f && no_split) {
-          k = run_steady32<OBS, K, FORM_F, false>(L, sav, c, tk, split, k, wl, f, impact_exit);
+          k = run_steady32<OBS, K, FORM_F, false, BATCH>(L, sav, c, tk, split, k, wl, f, impact_exit);
         } else if (steady_c) {
-          k = run_steady32<OBS, K, FORM_C, true>(L, sav, c, tk, split, k, wl, f, impact_exit);
+          k = run_steady32<OBS, K, FORM_C, true, BATCH>(L, sav, c, tk, split, k, wl, f, impact_exit);
         } else if (steady_f) {
-          k = run_steady32<OBS, K, FORM_F, true>(L, sav, c, tk, split, k, wl, f, impact_exit);
+          k = run_steady32<OBS, K, FORM_F, true, BATCH>(L, sav, c, tk, split, k, wl, f, impact_exit);
         } else if (steady_g) {  // both kinds: the generic form, whose step serves either
-          k = run_steady32<OBS, K, FORM_G, true>(L, sav, c, tk, split, k, wl, f, impact_exit);
+          k = run_steady32<OBS, K, FORM_G, true, BATCH>(L, sav, c, tk, split, k, wl, f, impact_exit);
         } else {
-          run_block32<OBS, K, true>(L, sav, c, split, splits & L.active, nd, k, wnd, impact_exit);
+          run_block32<OBS, K, run_pieces<K, true, BATCH>() == 1>(L, sav, c, split, splits & L.active, nd, k, wnd, impact_exit);
           k += K;
         }
       } else if (KM > KS && k % KM == 0 && k + KM <= wl &&
@@ -2119,7 +2134,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__
       if (K > RB) {
         const float tk = kr >= nd ? c.tb : c.td;  // one target over a block
         bool skip = go;
-        for (int it = 0; it < K / RB; ++it) {
+        for (int it = 0; it < run_pieces<K, true, BATCH>() * K / RB; ++it) {
           skip = skip && kr % RB == 0 && kr + RB <= se;
           if (ballot(skip) == 0) break;
           if (skip) {
@@ -2136,7 +2151,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__
           }
         }
       }
-      for (int it = 0; it < K; ++it) {
+      for (int it = 0; it < run_pieces<K, true, BATCH>() * K; ++it) {
         if (ballot(go) == 0) break;
         if (go) {
           const float vb = speed32<true>(r);
@@ -2673,7 +2688,15 @@ struct Shape {
 
 // spt: samples per lane of the kernel launched (a one-pass grid covers
 // n / spt lanes)
-Shape shape(const TuneCfg& t, int64_t n, int spt = 1) {
+// A persistent launch of fewer chunks than the grid has wavefronts would run
+// them all at once, some SIMDs one more than others; with as many wavefronts per
+// SIMD as there are whole chunks for (at least 2), the shortest chunks, which
+// are left over, go to the SIMDs that are done first.  FP64, kernel with 4 and
+// with 3: 200,000 samples 0.258 and 0.237 ms, with a lead 0.432 and 0.346, RK4
+// 1.50 and 1.29; 160,000 with 4 and with 2: 0.209 and 0.198.  Not under the
+// controller (spread: false), whose wavefronts wait on their draws: 200,000
+// samples 0.485 and 0.523.
+Shape shape(const TuneCfg& t, int64_t n, int spt = 1, bool spread = true) {
   static int cus = 0;
   if (cus == 0) {
     int dev = 0;
@@ -2686,7 +2709,11 @@ Shape shape(const TuneCfg& t, int64_t n, int spt = 1) {
   const int64_t per = static_cast<int64_t>(t.block) * spt;
   const int64_t need = (n + per - 1) / per;
   if (t.waves_per_simd > 0) {
-    const int64_t grid = static_cast<int64_t>(cus) * 4 * t.waves_per_simd * 64 / t.block;
+    const int64_t simds = static_cast<int64_t>(cus) * 4, chunks = (n + 64 * spt - 1) / (64 * spt);
+    int64_t waves = t.waves_per_simd;
+    if (spread && waves > 2 && chunks < waves * simds)
+      waves = chunks / simds > 2 ? chunks / simds : 2;
+    const int64_t grid = simds * waves * 64 / t.block;
     sh.grid = static_cast<unsigned>(need < grid ? need : grid);
     sh.persistent = 1;
   } else {
@@ -2849,7 +2876,7 @@ int integrate(const aeb_scenario& s0, int precision, const Bufs& b, int64_t n, c
   const int obs = s0.obstacle;
   Ctx ctx = ctx_in;
   const TuneCfg t = tune_get(precision == AEB_FP64 ? AEB_FP64 : AEB_FP32C, obs);
-  const Shape sh = shape(t, n);
+  const Shape sh = shape(t, n, 1, BATCH || !control_on(s0));
   if (!BATCH && control_on(s0)) {
     // the controller decides every ctl_period and blocks stay within a
     // decision period: the top level is a block size that divides the period
