@@ -487,6 +487,70 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_scatter(const uint32_t* keys, in
   }
 }
 
+// The whole sort of a small launch in one workgroup: histogram, scan and
+// placement in LDS, each thread's keys and ranks in registers.  One launch
+// instead of four (clear, histogram, scan, placement), whose fixed costs set the
+// time at such sizes: 25,000 keys 18 us against 19 us of kernels and the gaps
+// between them (the call 290 -> 272 us).  Up to SORT1_MAX keys: beyond, the
+// separate kernels spread over the chip.
+constexpr int SORT1_T = 1024;
+constexpr int SORT1_PER = 32;
+constexpr int64_t SORT1_MAX = static_cast<int64_t>(SORT1_T) * SORT1_PER;
+
+template <int NB>
+__global__ __launch_bounds__(SORT1_T) void k_sort1(const uint32_t* keys, int64_t n, uint32_t* perm,
+                                                   unsigned long long* counter,
+                                                   const BatchHdr* hdr) {
+  if (hdr) n = hdr->total;
+  __shared__ uint32_t cnt[NB];
+  __shared__ uint32_t wsum[SORT1_T / 64];
+  const int t = threadIdx.x;
+  if (t == 0) *counter = 0ull;
+  uint32_t key[SORT1_PER], rank[SORT1_PER];
+  // every key load in flight before the first LDS rank
+#pragma unroll
+  for (int r = 0; r < SORT1_PER; ++r) {
+    const int64_t i = static_cast<int64_t>(r) * SORT1_T + t;
+    key[r] = i < n ? keys[i] : 0u;
+  }
+  for (int j = t; j < NB; j += SORT1_T) cnt[j] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < SORT1_PER; ++r) {
+    const int64_t i = static_cast<int64_t>(r) * SORT1_T + t;
+    rank[r] = i < n ? atomicAdd(&cnt[key[r]], 1u) : 0u;
+  }
+  __syncthreads();
+  // exclusive scan of the counts, PER consecutive bins per thread
+  constexpr int PER = NB / SORT1_T;
+  uint32_t loc[PER], sum = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    loc[j] = cnt[t * PER + j];
+    sum += loc[j];
+  }
+  uint32_t inc = sum;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t v = __shfl_up(inc, o);
+    if ((t & 63) >= o) inc += v;
+  }
+  if ((t & 63) == 63) wsum[t >> 6] = inc;
+  __syncthreads();
+  uint32_t base = inc - sum;
+  for (int w = 0; w < (t >> 6); ++w) base += wsum[w];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    cnt[t * PER + j] = base;
+    base += loc[j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < SORT1_PER; ++r) {
+    const int64_t i = static_cast<int64_t>(r) * SORT1_T + t;
+    if (i < n) perm[cnt[key[r]] + rank[r]] = static_cast<uint32_t>(i);
+  }
+}
+
 __global__ void k_zero(uint32_t* p, int64_t n) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
@@ -2772,6 +2836,11 @@ size_t bufs_layout(int64_t n, int n_scn, bool lead, char* base, Bufs* b) {
 template <int NB = NBINS>
 void sort_keys(const Bufs& b, int64_t n, hipStream_t st, const BatchHdr* hdr = nullptr,
                bool hist = true) {
+  if (n <= SORT1_MAX) {
+    hipLaunchKernelGGL(k_sort1<NB>, dim3(1), dim3(SORT1_T), 0, st, b.keys, n, b.perm, b.counter,
+                       hdr);
+    return;
+  }
   const unsigned pblk = static_cast<unsigned>((n + PREP_SAMPLES - 1) / PREP_SAMPLES);
   if (hist)
     hipLaunchKernelGGL(k_hist<NB>, dim3(pblk), dim3(PREP_BLOCK), 0, st, b.keys, n, b.hist, hdr);
@@ -3017,7 +3086,9 @@ int launch_rollout_fast_into(const aeb_scenario& s, const ParamSrc* src, int pre
   const unsigned pblk = prep_grid(n) + (act ? 1 : 0);
   const bool ctl = control_on(s);
   const int nb = ctl ? NBINS_CTL : NBINS;
-  hipLaunchKernelGGL(k_zero, dim3(nb / 256), dim3(256), 0, st, b.hist, int64_t(nb));
+  // a small launch's sort takes its own histogram
+  const bool small = n <= SORT1_MAX;
+  if (!small) hipLaunchKernelGGL(k_zero, dim3(nb / 256), dim3(256), 0, st, b.hist, int64_t(nb));
   PrepArgs pa{};
   pa.s = s;
   pa.src = src ? *src : ParamSrc{};
@@ -3030,7 +3101,10 @@ int launch_rollout_fast_into(const aeb_scenario& s, const ParamSrc* src, int pre
   pa.weight = out.weight;
   pa.act = act;
   const unsigned cblk = static_cast<unsigned>((n + PREP_SAMPLES - 1) / PREP_SAMPLES);
-  if (src && ctl)
+  if (src && small)
+    hipLaunchKernelGGL((k_prep<false, false>), dim3(pblk), dim3(PREP_BLOCK), 0, st, pa, b.jobs,
+                       b.leads, b.keys);
+  else if (src && ctl)
     hipLaunchKernelGGL(k_prep_cols<NBINS_CTL>, dim3(cblk), dim3(PREP_BLOCK), 0, st, pa, b.jobs,
                        b.leads, b.keys, b.hist);
   else if (src)
@@ -3102,7 +3176,8 @@ int launch_batch_fast_into(const aeb_scenario* scns, int n_scn, int precision,
   // the prep's index space: each scenario padded to a multiple of 64 samples
   const int64_t padded = tab[n_scn - 1].poff + ((scns[n_scn - 1].n_samples + 63) & ~int64_t(63));
   const unsigned pblk = prep_grid(padded);
-  hipLaunchKernelGGL(k_zero, dim3(NBINS / 256), dim3(256), 0, st, b.hist, int64_t(NBINS));
+  if (total > SORT1_MAX)
+    hipLaunchKernelGGL(k_zero, dim3(NBINS / 256), dim3(256), 0, st, b.hist, int64_t(NBINS));
   PrepArgs pa{};
   pa.n = total;
   pa.cap = static_cast<float>(cap);
@@ -3131,7 +3206,8 @@ int launch_batch_fast_dev(const aeb_scenario& kind, bool perception, int precisi
   // the prep's index space for any mix within the capacity (each scenario
   // padded to a multiple of 64 samples)
   const unsigned pblk = prep_grid(cap_total + 63 * static_cast<int64_t>(cap_scn));
-  hipLaunchKernelGGL(k_zero, dim3(NBINS / 256), dim3(256), 0, st, b.hist, int64_t(NBINS));
+  if (cap_total > SORT1_MAX)
+    hipLaunchKernelGGL(k_zero, dim3(NBINS / 256), dim3(256), 0, st, b.hist, int64_t(NBINS));
   PrepArgs pa{};
   pa.n = cap_total;
   pa.cap = 1.0f;
