@@ -49,6 +49,7 @@ struct Block {
   hipStream_t last = nullptr;
   bool busy = false;           // held by a live scope
   bool fenced = false;         // ev has been recorded
+  aeb_stats* pin = nullptr;    // pinned host memory that goes with the block
 };
 constexpr int MAX_DEV = 64;
 constexpr size_t POOL_SOFT = 8;
@@ -124,6 +125,12 @@ Block* acquire(int dev, size_t bytes, hipStream_t st) {
       return nullptr;
     }
     pick->bytes = want;
+    // (without it the statistics are copied to the caller's memory)
+    if (!pick->pin && hipHostMalloc(reinterpret_cast<void**>(&pick->pin), sizeof(aeb_stats),
+                                    hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      pick->pin = nullptr;
+    }
   }
   if (wait && hipStreamWaitEvent(st, pick->ev, 0) != hipSuccess) {
     set_error("scratch: hipStreamWaitEvent failed");
@@ -184,6 +191,12 @@ void* scratch_slot(int slot, size_t bytes, hipStream_t stream) {
   if (!b) return nullptr;
   sc->held_[slot] = b;
   return b->ptr;
+}
+
+aeb_stats* pool_stats() {
+  ScratchScope* sc = g_scope;
+  const Block* b = sc ? static_cast<const Block*>(sc->held_[0]) : nullptr;
+  return b ? b->pin : nullptr;
 }
 
 // ---------------------------------------------------------------------------

@@ -47,6 +47,7 @@ class ScratchScope {
 
  private:
   friend void* scratch_slot(int slot, size_t bytes, hipStream_t stream);
+  friend aeb_stats* pool_stats();
   hipStream_t st_;
   int dev_ = -1;
   ScratchScope* outer_;
@@ -54,6 +55,10 @@ class ScratchScope {
 };
 void* scratch_slot(int slot, size_t bytes, hipStream_t stream);
 inline void* pool_block(size_t bytes, hipStream_t stream) { return scratch_slot(0, bytes, stream); }
+// pinned host memory for one set's statistics that goes with the block the
+// current scope holds, or nullptr; another call may use it once the scope has
+// ended, so the caller waits for its work before that
+aeb_stats* pool_stats();
 
 // events around the integration kernel (aeb_timing_enable)
 void timing_begin(hipStream_t stream);
