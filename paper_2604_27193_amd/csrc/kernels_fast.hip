@@ -12,19 +12,22 @@
 //  2. counting sort of the keys: samples with the same predicted length land
 //     in the same wavefront, longest first, so a wavefront's lanes finish
 //     together and long wavefronts start early.
-//  3. rollout: each lane integrates one sample.  Steps run in unchecked
-//     blocks of K steps whenever no lane can stop, reach the horizon or pass
-//     its command switch inside the block (guaranteed by per-lane bounds; the
-//     switch is the dead time, plus the sample's own perception delay when
-//     the scenario has one, and then the sort groups equal switch steps);
-//     otherwise single steps with every test.  Inside a block the step takes
-//     the cheapest form that gives bit-identical results in the current
-//     phase: dead time (a = 0), generic, never-limited (max(a, alim) = a) or
-//     friction-limited (max(a, alim) = alim for good, actuator update dead).
-//     A crossing of the obstacle inside a block is found afterwards by
-//     replaying that block from its saved start state.  The grid is
-//     persistent: each wavefront claims the next 64 sorted samples through an
-//     atomic counter until none are left (longest first, dynamically balanced).
+//     (Up to SORT1_MAX samples one workgroup sorts.)
+//  3. rollout: each lane integrates one sample.  Steps run in blocks without
+//     per-step tests (K steps; 16, then 4 as the wavefront nears its limits,
+//     then single steps), in none of which a running lane can reach the horizon
+//     or pass its command switch (the switch is the dead time, plus the
+//     sample's own perception delay when the scenario has one, and then the sort
+//     groups equal switch steps).  A lane may stop, or pass the obstacle, inside
+//     a block: both are found at the block's end and the lane's end is
+//     recomputed by replaying the block from its start, saved in LDS, while the
+//     other lanes go on.  Inside a block the step takes the cheapest form that
+//     gives bit-identical results in the current phase: dead time (a = 0),
+//     generic, never-limited (max(a, alim) = a) or friction-limited
+//     (max(a, alim) = alim for good, actuator update dead).  The grid is one
+//     pass over the samples, or persistent: each wavefront takes its first chunk
+//     of 64 sorted samples by its place and claims further ones through an
+//     atomic counter (longest first, dynamically balanced).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -46,9 +49,9 @@ namespace {
 #define HOT __device__ __attribute__((always_inline)) inline
 
 // sort keys: 2 classes x 4,096 length levels (with perception 64 coarse length
-// bins x 64 levels of length and command step); with the controller 64 decision ticks x 2 classes x 128 length levels (the sort's
-// kernels take the key count as a template argument: their per-bin loops
-// cost latency on small launches)
+// bins x 64 levels of length and command step); with the controller 64 decision
+// ticks x 2 classes x 128 length levels (the sort's kernels take the key count
+// as a template argument: their per-bin loops cost latency on small launches)
 constexpr int NBINS = 8192;
 constexpr int NBINS_CTL = 16384;
 // The sort's kernels (prep, scan, scatter) run in workgroups of one wavefront
@@ -2830,7 +2833,7 @@ size_t bufs_layout(int64_t n, int n_scn, bool lead, char* base, Bufs* b) {
   return total;
 }
 
-// sort the prepared keys into the permutation (the scan zeroes the claim counter)
+// sort the prepared keys into the permutation (and zero the claim counter)
 // (hdr: a recorded mix, n its capacity and the actual count on the device)
 // (hist: the key histogram still to be taken; the plain method's prep takes it)
 template <int NB = NBINS>

@@ -11,7 +11,7 @@
 // collected and the rank selected among them in LDS (a radix select over an
 // order-preserving map of the FP64 bit patterns).  A bin with more than 8,192
 // elements falls back to a radix select over the whole array (8 passes of 8
-// bits).
+// bits; the sets of a batch that need it go through the passes together).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
