@@ -35,7 +35,9 @@ sys.path.insert(0, ROOT)
 METRIC = "rollouts/sec FP64 vs FP32-comp; p50/p99 latency of 25k-sample requests"
 FP64_VECTOR_PEAK_TFLOPS = 78.6   # 256 CU x 4 SIMD x 16 lanes x 2 flop x 2.4 GHz
 FP64_FLOP_PER_CYCLE = 32768       # 1,024 SIMDs x 16 lanes x 2 flop
-FP32_VECTOR_PEAK_TFLOPS = 157.3  # packed FP32; unpacked FP32 issues at the FP64 rate
+# FP32 vector: an unpacked FMA, add or multiply measured at 2.05-2.3 cycles per wavefront
+# instruction (the 2 cycles of this peak), against 4.4-5.3 in FP64
+FP32_VECTOR_PEAK_TFLOPS = 157.3
 EULER_FLOPS_PER_STEP = 11        # 4 fma (2 each) + 3 (v*v, -c, cmd-a)
 FP32C_FLOPS_PER_STEP = 9         # 4 fma + v*v, compensated sums per block not counted
 RK4_FLOPS_PER_STEP = 57          # 4 stage speed/actuator derivatives (6 each), 3 stage
@@ -574,7 +576,7 @@ def uneven_config_leg(B, W, torch, reps=3):
                                   risk=RISK, margin_q=MARGIN_Q, grid=GRID)
         eager_ms = (time.perf_counter() - t0) / reps * 1e3
         # the batched integration kernel alone (library HIP events) and its
-        # lane accounting: FP32C rate against the unpacked and packed peaks
+        # lane accounting: FP32C rate against the FP32 vector peak
         steps_total = sum(int(o["steps"].long().sum().item()) for o in outs)
         B.timing_enable(True)
         try:
@@ -623,8 +625,7 @@ def uneven_config_leg(B, W, torch, reps=3):
                       "candidates": len(ranked), "default_shape_ms": default_ms},
             "kernel_ms": kern_ms, "kernel_rollouts_per_s": total / (kern_ms * 1e-3),
             "steps_per_launch": steps_total, "achieved_tflops": tflops,
-            "frac_unpacked_fp32_peak": tflops / FP64_VECTOR_PEAK_TFLOPS,
-            "frac_packed_fp32_peak": tflops / FP32_VECTOR_PEAK_TFLOPS,
+            "frac_fp32_peak": tflops / FP32_VECTOR_PEAK_TFLOPS,
             "lane_efficiency": steps_total / wave if wave else None,
             "eager_ms_per_step": eager_ms, "eager_rollouts_per_s": total / (eager_ms * 1e-3),
             "graph_ms_per_step": graph_ms, "graph_rollouts_per_s": total / (graph_ms * 1e-3),
@@ -1046,13 +1047,8 @@ def main():
             "kernel_rollouts_per_s": n / kavg32,
             "rollout_call_ms": float(np.mean(c32)),
             "achieved_tflops": FP32C_FLOPS_PER_STEP * steps32 / kavg32 / 1e12,
-            # the build disables packed FP32 instructions, so FP32 issues at the
-            # unpacked rate (the FP64 rate, 78.6 TFLOP/s), half the packed peak
-            "peak_tflops_unpacked_fp32": FP64_VECTOR_PEAK_TFLOPS,
-            "frac_unpacked_fp32_peak": FP32C_FLOPS_PER_STEP * steps32 / kavg32 / 1e12
-                                       / FP64_VECTOR_PEAK_TFLOPS,
-            "frac_packed_fp32_peak": FP32C_FLOPS_PER_STEP * steps32 / kavg32 / 1e12
-                                     / FP32_VECTOR_PEAK_TFLOPS,
+            "frac_fp32_peak": FP32C_FLOPS_PER_STEP * steps32 / kavg32 / 1e12
+                              / FP32_VECTOR_PEAK_TFLOPS,
             "max_rel_dist_err_vs_fp64": rel32,
             "boundary_samples": int(inband.sum()),
             "collision_flags_equal_fp64_outside_band": flags_equal,

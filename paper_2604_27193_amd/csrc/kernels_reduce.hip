@@ -1557,7 +1557,7 @@ int launch_reduce(const OutCols& out, int64_t n, const aeb_reduce_req& req, aeb_
   // The statistics come by way of the library's pinned memory, written by a
   // kernel: a copy to pageable memory starts only once the kernels are done, and
   // a copy engine has a start of its own (25,000 samples, rollout and reduction:
-  // 275 us with the copy, 255 with a copy to pinned memory, 242 so).
+  // 275 us with the copy, 256 with a copy to pinned memory, 242 so).
   aeb_stats* pin = pool_stats();
   int rc;
   if (pin) {
