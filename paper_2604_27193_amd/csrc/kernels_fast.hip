@@ -493,14 +493,16 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_scatter(const uint32_t* keys, in
 // The whole sort of a small launch in one workgroup: histogram, scan and
 // placement in LDS, each thread's keys and ranks in registers.  One launch
 // instead of four (clear, histogram, scan, placement), whose fixed costs set the
-// time at such sizes: 25,000 keys 18 us against 19 us of kernels and the gaps
-// between them (the call 290 -> 272 us).  Up to SORT1_MAX keys: beyond, the
-// separate kernels spread over the chip.
+// time at such sizes: 25,000 keys 12 us against 19 us of kernels and the gaps
+// between them, 1,000 keys 3.7 us (the call with four launches 290 and 284 us, with
+// one 272 and 266).  Up to SORT1_MAX keys: beyond, the separate kernels spread
+// over the chip.
 constexpr int SORT1_T = 1024;
 constexpr int SORT1_PER = 32;
 constexpr int64_t SORT1_MAX = static_cast<int64_t>(SORT1_T) * SORT1_PER;
 
-template <int NB>
+// SPT: samples per thread
+template <int NB, int SPT>
 __global__ __launch_bounds__(SORT1_T) void k_sort1(const uint32_t* keys, int64_t n, uint32_t* perm,
                                                    unsigned long long* counter,
                                                    const BatchHdr* hdr) {
@@ -509,17 +511,17 @@ __global__ __launch_bounds__(SORT1_T) void k_sort1(const uint32_t* keys, int64_t
   __shared__ uint32_t wsum[SORT1_T / 64];
   const int t = threadIdx.x;
   if (t == 0) *counter = 0ull;
-  uint32_t key[SORT1_PER], rank[SORT1_PER];
+  uint32_t key[SPT], rank[SPT];
   // every key load in flight before the first LDS rank
 #pragma unroll
-  for (int r = 0; r < SORT1_PER; ++r) {
+  for (int r = 0; r < SPT; ++r) {
     const int64_t i = static_cast<int64_t>(r) * SORT1_T + t;
     key[r] = i < n ? keys[i] : 0u;
   }
   for (int j = t; j < NB; j += SORT1_T) cnt[j] = 0;
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < SORT1_PER; ++r) {
+  for (int r = 0; r < SPT; ++r) {
     const int64_t i = static_cast<int64_t>(r) * SORT1_T + t;
     rank[r] = i < n ? atomicAdd(&cnt[key[r]], 1u) : 0u;
   }
@@ -548,9 +550,25 @@ __global__ __launch_bounds__(SORT1_T) void k_sort1(const uint32_t* keys, int64_t
   }
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < SORT1_PER; ++r) {
+  for (int r = 0; r < SPT; ++r) {
     const int64_t i = static_cast<int64_t>(r) * SORT1_T + t;
-    if (i < n) perm[cnt[key[r]] + rank[r]] = static_cast<uint32_t>(i);
+    rank[r] = i < n ? cnt[key[r]] + rank[r] : ~0u;
+  }
+  // The permutation by way of LDS, in the counters' place, and from there in
+  // whole lines: one CU takes a cycle per line of a scattered store (25,000 keys
+  // placed by scattered stores 18 us, so 12).
+  uint16_t* stage = reinterpret_cast<uint16_t*>(cnt);
+  constexpr uint32_t STAGE = 2 * NB;
+  static_assert(SORT1_MAX <= 65536, "a sample's index fits 16 bits");
+  for (uint32_t lo = 0; lo < n; lo += STAGE) {
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < SPT; ++r) {
+        if (rank[r] - lo < STAGE && rank[r] != ~0u)
+        stage[rank[r] - lo] = static_cast<uint16_t>(r * SORT1_T + t);
+    }
+    __syncthreads();
+    for (uint32_t j = t; j < STAGE && lo + j < n; j += SORT1_T) perm[lo + j] = stage[j];
   }
 }
 
@@ -2840,8 +2858,13 @@ template <int NB = NBINS>
 void sort_keys(const Bufs& b, int64_t n, hipStream_t st, const BatchHdr* hdr = nullptr,
                bool hist = true) {
   if (n <= SORT1_MAX) {
-    hipLaunchKernelGGL(k_sort1<NB>, dim3(1), dim3(SORT1_T), 0, st, b.keys, n, b.perm, b.counter,
-                       hdr);
+    // (the unrolled samples past n cost: 1,000 samples 6.3 us with 32 a thread)
+    if (n <= SORT1_T * 8)
+      hipLaunchKernelGGL((k_sort1<NB, 8>), dim3(1), dim3(SORT1_T), 0, st, b.keys, n, b.perm,
+                         b.counter, hdr);
+    else
+      hipLaunchKernelGGL((k_sort1<NB, SORT1_PER>), dim3(1), dim3(SORT1_T), 0, st, b.keys, n,
+                         b.perm, b.counter, hdr);
     return;
   }
   const unsigned pblk = static_cast<unsigned>((n + PREP_SAMPLES - 1) / PREP_SAMPLES);

@@ -1,5 +1,5 @@
 """Launch sizes around the one-workgroup sort (up to 32,768 keys, 1,024 at a
-time): FP64 with host-drawn parameters equals the reference bit for bit, drawn
+time, 8 or 32 a thread, placed 16,384 or 32,768 at a time): FP64 with host-drawn parameters equals the reference bit for bit, drawn
 samples equal the same samples given as columns, a batch equals its scenarios one
 by one."""
 import numpy as np
@@ -10,7 +10,7 @@ from test_gpu_parity import check_fp64, plain, to_np, upload
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [1, 63, 1023, 1024, 1025, 16385, 32767, 32768, 32769]
+SIZES = [1, 63, 1023, 1024, 1025, 8192, 8193, 16384, 16385, 32767, 32768, 32769]
 
 
 @pytest.fixture(scope="module")
