@@ -1276,7 +1276,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
         run_block64<OBS, B, INTEG, CTL, TOP, TAB, false>(
             L, sav, J, al, c, kk, wnd, ctx.impact_exit, ctx.ca.a_warn, xmax, at);
     };
-    // every lane has ended by its step nmax (the horizon test fires at k + 1 == nmax)
+    // every lane has ended by its step nmax (the horizon test fires at k + 1 = nmax)
     while (L.active) {
       // the step index is the same in every lane: keep it (and the branches on it) scalar
       k = __builtin_amdgcn_readfirstlane(k);
@@ -1394,7 +1394,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
               end = AEB_END_IMPACT;
             else if (L.s.v <= 0.0)
               end = AEB_END_STOP;
-            else if (k + 1 == c.nmax)
+            else if (k + 1 >= c.nmax)
               end = AEB_END_HORIZON;
             done = end != 0;
             if (done) {
@@ -1748,7 +1748,7 @@ __global__ __launch_bounds__(256) void k_roll_fp64x2(const Job* __restrict__ job
               end[q] = AEB_END_STOP;
               steps[q] = k + 1;
               dist[q] = L[q].s.x;
-            } else if (k + 1 == c[q].nmax) {
+            } else if (k + 1 >= c[q].nmax) {
               L[q].active = false;
               end[q] = AEB_END_HORIZON;
               steps[q] = k + 1;
@@ -2011,24 +2011,31 @@ HOT bool long_block32(const Wave32& L, float thr, lanes_t fall) {
   return (low & ~fall) == 0 && (ballot(v > 2.0f * thr) & L.active) != 0;
 }
 
-// K-step pieces of a run between its tests: two, unrolled, for split speeds in a
-// batched launch, whose wavefronts are long and many, so that the tests' share is
-// worth a longer replay of the block with the crossing or the stop (1,000
-// uneven scenarios, most of their steps split: kernel 32.4 -> 30.4 ms); one
-// elsewhere (1,048,576 samples of one scenario 0.575 ms, 0.59 with two;
+// K-step pieces of a run between its tests: two, unrolled, for a wavefront with
+// split speeds in a batched launch, whose wavefronts are long and many, so that
+// the tests' share is worth a longer replay of the block with the crossing or the
+// stop (1,000 uneven scenarios, most of their steps split: kernel 32.4 -> 30.4
+// ms); one elsewhere (1,048,576 samples of one scenario 0.575 ms, 0.59 with two;
 // 200,000 0.157 and 0.165).
-template <int K, bool SPLIT, bool BATCH>
-constexpr int run_pieces() { return SPLIT && BATCH && K == FLUSH ? 2 : 1; }
+template <int K, bool BATCH>
+constexpr int run_pieces() { return BATCH && K == FLUSH ? 2 : 1; }
+
+// Whether U pieces from step k stay below the block limit wl with every stop
+// inside them found at their end: asked before each of a run's rounds, the first
+// included.
+template <int K, int U>
+HOT bool run_fits32(const Wave32& L, const L32& c, int k, int wl, lanes_t fall) {
+  return k + U * K <= wl && long_block32(L, U * c.thr, fall);
+}
 
 // Consecutive K-step blocks in one steady form, SPLIT if any lane's speed is
-// split (as run_steady of the FP64 kernel), with the flush at every flush
-// point.  (Two blocks per round of tests, the second in a rolled loop: no
-// faster for one wavefront on its SIMD, and 35 more VGPRs.)
-template <int OBS, int K, int FORM, bool SPLIT, bool BATCH>
+// split, U of them between tests (as run_steady of the FP64 kernel), with the
+// flush at every flush point.  The caller has asked run_fits32 of the first U.
+// (Two blocks per round of tests, the second in a rolled loop: no faster for one
+// wavefront on its SIMD, and 35 more VGPRs.)
+template <int OBS, int K, int FORM, bool SPLIT, int U>
 HOT int run_steady32(Wave32& L, Saves32<OBS>& S, const L32& c, float tk, bool split, int k,
                      int wl, lanes_t fall, int impact_exit) {
-  constexpr int U = run_pieces<K, SPLIT, BATCH>();
-  bool more;
   do {
     k = __builtin_amdgcn_readfirstlane(k);
     save_start32<OBS>(L, S);
@@ -2043,8 +2050,7 @@ HOT int run_steady32(Wave32& L, Saves32<OBS>& S, const L32& c, float tk, bool sp
     }
     block_events32<OBS>(L, S, c, k, U * K, impact_exit);
     k += U * K;
-    more = k + U * K <= wl && L.active != 0 && long_block32(L, U * c.thr, fall);
-  } while (more);
+  } while (L.active != 0 && run_fits32<K, U>(L, c, k, wl, fall));
   return k;
 }
 
@@ -2127,24 +2133,35 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__
         // of blocks
         const lanes_t f = falling32(L.s, c, tk);
         const bool no_split = (splits & L.active) == 0;
-        constexpr int U = run_pieces<K, true, BATCH>();
-        const bool past = k + K > wnd && (no_split || U == 1 ||
-                                          (k + U * K <= wl && long_block32(L, U * c.thr, f)));
+        // (one piece fits: just tested; U of them before a run with split speeds)
+        constexpr int U = run_pieces<K, BATCH>();
+        const bool past =
+            k + K > wnd && (no_split || U == 1 || run_fits32<K, U>(L, c, k, wl, f));
         const bool steady_c = past && (L.active & ~L.clamped) == 0;
         const bool steady_f = past && !steady_c && (L.active & ~L.free_lane) == 0;
         const bool steady_g = past && (L.active & ~(L.clamped | L.free_lane)) == 0;
+        auto run = [&](auto form, auto with_split, auto pieces) {
+          k = run_steady32<OBS, K, decltype(form)::value, decltype(with_split)::value,
+                           decltype(pieces)::value>(L, sav, c, tk, split, k, wl, f, impact_exit);
+        };
+        using one = std::integral_constant<int, 1>;
+        using more = std::integral_constant<int, U>;
         if (steady_c && no_split) {
-          k = run_steady32<OBS, K, FORM_C, false, BATCH>(L, sav, c, tk, split, k, wl, f, impact_exit);
+          run(std::integral_constant<int, FORM_C>(), std::false_type(), one());
         } else if (steady_f && no_split) {
-          k = run_steady32<OBS, K, FORM_F, false, BATCH>(L, sav, c, tk, split, k, wl, f, impact_exit);
+          run(std::integral_constant<int, FORM_F>(), std::false_type(), one());
         } else if (steady_c) {
-          k = run_steady32<OBS, K, FORM_C, true, BATCH>(L, sav, c, tk, split, k, wl, f, impact_exit);
+          run(std::integral_constant<int, FORM_C>(), std::true_type(), more());
         } else if (steady_f) {
-          k = run_steady32<OBS, K, FORM_F, true, BATCH>(L, sav, c, tk, split, k, wl, f, impact_exit);
-        } else if (steady_g) {  // both kinds: the generic form, whose step serves either
-          k = run_steady32<OBS, K, FORM_G, true, BATCH>(L, sav, c, tk, split, k, wl, f, impact_exit);
+          run(std::integral_constant<int, FORM_F>(), std::true_type(), more());
+        } else if (steady_g && (no_split || U == 1)) {
+          // both kinds: the generic form, whose step serves either
+          run(std::integral_constant<int, FORM_G>(), std::true_type(), one());
+        } else if (steady_g) {
+          run(std::integral_constant<int, FORM_G>(), std::true_type(), more());
         } else {
-          run_block32<OBS, K, run_pieces<K, true, BATCH>() == 1>(L, sav, c, split, splits & L.active, nd, k, wnd, impact_exit);
+          run_block32<OBS, K, U == 1>(L, sav, c, split, splits & L.active, nd, k, wnd,
+                                      impact_exit);
           k += K;
         }
       } else if (KM > KS && k % KM == 0 && k + KM <= wl &&
@@ -2177,7 +2194,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__
           if (end == 0) {
             if (v <= 0.0f)
               end = AEB_END_STOP;
-            else if (k + 1 == nmax)
+            else if (k + 1 >= nmax)
               end = AEB_END_HORIZON;
           }
           done = end != 0;
@@ -2219,7 +2236,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__
       if (K > RB) {
         const float tk = kr >= nd ? c.tb : c.td;  // one target over a block
         bool skip = go;
-        for (int it = 0; it < run_pieces<K, true, BATCH>() * K / RB; ++it) {
+        for (int it = 0; it < run_pieces<K, BATCH>() * K / RB; ++it) {
           skip = skip && kr % RB == 0 && kr + RB <= se;
           if (ballot(skip) == 0) break;
           if (skip) {
@@ -2236,7 +2253,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__
           }
         }
       }
-      for (int it = 0; it < run_pieces<K, true, BATCH>() * K; ++it) {
+      for (int it = 0; it < run_pieces<K, BATCH>() * K; ++it) {
         if (ballot(go) == 0) break;
         if (go) {
           const float vb = speed32<true>(r);
@@ -2629,7 +2646,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c_lead(const Job* __restr
             end = AEB_END_IMPACT;
           } else if (v <= 0.0f) {
             end = AEB_END_STOP;
-          } else if (k + 1 == nmax) {
+          } else if (k + 1 >= nmax) {
             end = AEB_END_HORIZON;
           }
           done = end != 0;

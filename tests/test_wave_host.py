@@ -1,0 +1,66 @@
+"""The integration kernels' control flow on the CPU: their own source on 64
+emulated lanes (wave64/).  A scenario's samples in a batched launch, whatever
+wavefronts they share, equal its launch alone bit for bit, every launch ends,
+and none runs past a block limit (a horizon, a command switch)."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2604_27193_amd import workloads as W
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("wave") / "roll_check")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-ffp-contract=off",
+                        "-I", os.path.join(HERE, "wave64"), "-I", os.path.join(ROOT, "include"),
+                        "-I", os.path.join(ROOT, "paper_2604_27193_amd", "csrc"),
+                        os.path.join(HERE, "wave64", "roll_check.cpp"), "-o", out],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return out
+
+
+def limited_and_not(other=None, **over):
+    """32 friction-limited samples and 32 never limited, in one wavefront; none
+    long enough for split speeds.  `other`: overrides of the second scenario."""
+    over.setdefault("v0", ("trunc_normal", 18.0, 1.0, 15.0, 21.0))
+    a = W.single(32, seed=9, mu=("const", 0.45), **over)
+    return [a, dict(a, scenario_id=1, mu=("const", 0.85), **(other or {}))]
+
+
+# each pair of limits leaves both remainders of the 128 steps that two blocks take
+LIMITS = {f"horizon_{h}": limited_and_not(horizon=h * 1e-3) for h in (1300, 1364, 1500, 1564)}
+LIMITS.update({f"command_{t}": limited_and_not({"dead_time": t}) for t in
+               (0.26, 0.34, 0.46, 0.6, 0.66, 0.75)})
+LIMITS["steps"] = limited_and_not({"dt": 2e-3}, horizon=1.5)
+# no lane can stop: downhill beyond what the brake holds
+for _h in (1500, 1564):
+    LIMITS[f"downhill_{_h}"] = limited_and_not(horizon=_h * 1e-3, grade=("const", -0.3),
+                                               a_cmd=-2.0)
+    LIMITS[f"downhill_{_h}"][0]["mu"] = ("const", 0.15)
+LIMITS["perception"] = [dict(W.perception(n, seed=6, scenario_id=j), mu=("uniform", 0.35, 1.0),
+                             v0=("trunc_normal", 18.0, 1.0, 15.0, 21.0))
+                        for j, n in enumerate((40, 65, 23))]
+OBSTACLES = {"none": {"obstacle": "none"}, "stationary": {}, "exit": {"impact_exit": True},
+             "lead": {"obstacle": "lead", "lead_decel": ("normal", 3.0, 0.5)}}
+
+
+@pytest.mark.parametrize("obstacle", sorted(OBSTACLES))
+@pytest.mark.parametrize("kernel", ["fp32c", "fp64", "fp64x2"])
+def test_batch_equals_alone(exe, tmp_path, kernel, obstacle):
+    from paper_2604_27193_amd import binding
+    if kernel == "fp64x2" and obstacle == "lead":
+        pytest.skip("two samples per lane: no lead vehicle")
+    files = []
+    for name, scns in LIMITS.items():
+        files.append(tmp_path / name)
+        files[-1].write_bytes(b"".join(bytes(binding.scenario(dict(d, **OBSTACLES[obstacle])))
+                                       for d in scns))
+    r = subprocess.run([exe, kernel, *map(str, files)], capture_output=True, text=True,
+                       timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
