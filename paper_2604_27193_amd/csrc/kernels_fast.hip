@@ -2140,25 +2140,27 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__
         const bool steady_c = past && (L.active & ~L.clamped) == 0;
         const bool steady_f = past && !steady_c && (L.active & ~L.free_lane) == 0;
         const bool steady_g = past && (L.active & ~(L.clamped | L.free_lane)) == 0;
-        auto run = [&](auto form, auto with_split, auto pieces) {
-          k = run_steady32<OBS, K, decltype(form)::value, decltype(with_split)::value,
-                           decltype(pieces)::value>(L, sav, c, tk, split, k, wl, f, impact_exit);
-        };
-        using one = std::integral_constant<int, 1>;
-        using more = std::integral_constant<int, U>;
+        // (calls, not a lambda that captures k: 1,048,576 samples without an
+        // obstacle 0.493 against 0.528 ms)
         if (steady_c && no_split) {
-          run(std::integral_constant<int, FORM_C>(), std::false_type(), one());
+          k = run_steady32<OBS, K, FORM_C, false, 1>(L, sav, c, tk, split, k, wl, f,
+                                                     impact_exit);
         } else if (steady_f && no_split) {
-          run(std::integral_constant<int, FORM_F>(), std::false_type(), one());
+          k = run_steady32<OBS, K, FORM_F, false, 1>(L, sav, c, tk, split, k, wl, f,
+                                                     impact_exit);
         } else if (steady_c) {
-          run(std::integral_constant<int, FORM_C>(), std::true_type(), more());
+          k = run_steady32<OBS, K, FORM_C, true, U>(L, sav, c, tk, split, k, wl, f,
+                                                     impact_exit);
         } else if (steady_f) {
-          run(std::integral_constant<int, FORM_F>(), std::true_type(), more());
+          k = run_steady32<OBS, K, FORM_F, true, U>(L, sav, c, tk, split, k, wl, f,
+                                                     impact_exit);
         } else if (steady_g && (no_split || U == 1)) {
           // both kinds: the generic form, whose step serves either
-          run(std::integral_constant<int, FORM_G>(), std::true_type(), one());
+          k = run_steady32<OBS, K, FORM_G, true, 1>(L, sav, c, tk, split, k, wl, f,
+                                                     impact_exit);
         } else if (steady_g) {
-          run(std::integral_constant<int, FORM_G>(), std::true_type(), more());
+          k = run_steady32<OBS, K, FORM_G, true, U>(L, sav, c, tk, split, k, wl, f,
+                                                     impact_exit);
         } else {
           run_block32<OBS, K, U == 1>(L, sav, c, split, splits & L.active, nd, k, wnd,
                                       impact_exit);
