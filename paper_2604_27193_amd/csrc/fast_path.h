@@ -17,7 +17,7 @@ struct Job {
   double alim;    // friction limit (negative)
   double kt;      // dt / tau (explicit Euler) or 1 / tau (RK4)
   double gap;     // initial gap to the obstacle
-  double dmax;    // bound on |dv/dt| over the whole rollout
+  double dmax;    // bound on |dv/dt| over the whole rollout (infinite: none)
   float pred;     // predicted number of steps
   uint32_t scn;   // scenario of the sample in a batched launch
 };

@@ -219,6 +219,16 @@ HOT uint32_t prep_sample(const PrepArgs& a, int64_t i, uint32_t j, int64_t local
   const double vmax = fabs(v0) + s.horizon * creach;
   const double brake = fmin(fabs(s.a_cmd), fabs(k.alim));
   J.dmax = (brake + fabs(k.kd) * vmax * vmax + fabs(k.c)) * 1.0001 + 1e-9;
+  // That supposes a brake between zero and its command over every step, and the
+  // Euler kernels' steady forms one that approaches the command from one side:
+  // an Euler step of at most one time constant, an RK4 step (whose mean brake
+  // stays there while it is stable, to 2.785) of at most 2.5.  Columns may hold
+  // other time constants, and so may RK4's draws: no bound then, so that the
+  // sample's wavefront takes single steps in the generic form, with every test,
+  // for as long as the sample runs.
+  const bool rk4 = s.integrator == AEB_RK4;
+  const double z = rk4 ? J.kt * s.dt : J.kt;
+  if (!(z >= 0.0 && z <= (rk4 ? 2.5 : 1.0))) J.dmax = INFINITY;
   // classify and predict
   const bool limited = !(k.alim < s.a_cmd - 1e-6);
   float td = static_cast<float>(ndl) * static_cast<float>(s.dt);
@@ -1237,7 +1247,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
     // limited for good once a <= alim: a never climbs above max(a, a_cmd) <
     // alim.  Both need an actuator that approaches its command from one side,
     // RK4's stages included: a step of at most one time constant (beyond it
-    // the lane keeps the generic form).
+    // an RK4 lane keeps the generic form, and an Euler lane the single steps).
     const bool smooth = ktdt >= 0.0 && ktdt <= 1.0;
     L.free_lane = ballot(smooth && J.alim < c.a_cmd - 1e-6);
     L.limited = ballot(smooth && J.alim > c.a_cmd + 1e-9);

@@ -64,3 +64,41 @@ def test_batch_equals_alone(exe, tmp_path, kernel, obstacle):
     r = subprocess.run([exe, kernel, *map(str, files)], capture_output=True, text=True,
                        timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+# One sample per scenario, so that alone each runs in a wavefront of its own;
+# actuator steps from a quarter of the time constant to beyond where the update
+# diverges (parameter columns may hold any; explicit Euler's draws are refused).
+def stiff(**over):
+    d = dict(v0=("uniform", 0.5, 2.5), mu=("uniform", 0.3, 1.0), gap=("uniform", 0.1, 0.5),
+             grade=("normal", 0.0, 0.1))
+    d.update(over)
+    return [W.single(1, seed=5, scenario_id=j, **d) for j in range(64)]
+
+
+STIFF = {"euler": stiff(horizon=0.4, tau=("uniform", 4e-4, 4e-3)),
+         "euler_diverging": stiff(horizon=0.3, tau=("uniform", 3e-4, 2e-3),
+                                  v0=("uniform", 1.0, 10.0)),
+         "rk4": stiff(horizon=1.5, dt=5e-3, integrator="rk4", tau=("uniform", 1.9e-3, 2e-2)),
+         "rk4_diverging": stiff(horizon=1.0, dt=5e-3, integrator="rk4",
+                                tau=("uniform", 1.3e-3, 3e-3), v0=("uniform", 1.0, 10.0))}
+
+
+@pytest.mark.parametrize("kernel,obstacle", [("fp64", "none"), ("fp64", "exit"), ("fp64", "lead"),
+                                             ("fp64x2", "none"), ("fp64x2", "stationary"),
+                                             ("fp32c", "none"), ("fp32c", "stationary"),
+                                             ("fp32c", "lead")])
+def test_stiff_actuator(exe, tmp_path, kernel, obstacle):
+    """A sample's result does not depend on its wavefront, however long its step
+    is against its actuator's time constant."""
+    from paper_2604_27193_amd import binding
+    files = []
+    for name, scns in STIFF.items():
+        if name.startswith("rk4") and (kernel != "fp64" or obstacle == "lead"):
+            continue
+        files.append(tmp_path / name)
+        files[-1].write_bytes(b"".join(bytes(binding.scenario(dict(d, **OBSTACLES[obstacle])))
+                                       for d in scns))
+    r = subprocess.run([exe, kernel, *map(str, files)], capture_output=True, text=True,
+                       timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
