@@ -1252,7 +1252,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
     L.free_lane = ballot(smooth && J.alim < c.a_cmd - 1e-6);
     L.limited = ballot(smooth && J.alim > c.a_cmd + 1e-9);
     int end = 0, steps = 0;
-    double dist = 0.0;
+    double dist = __builtin_nan("");  // until the lane's end is found
     // RK4's last step may move the position back (stage speeds below zero as
     // the vehicle stops): the margin then comes from the largest position,
     // tracked at block ends and over checked steps (before a stop the position
@@ -1512,7 +1512,8 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
       }
       lanes_join();
       if (OBS != AEB_OBS_NONE) L.collided |= ballot(passed);
-      if (go) vimp = __builtin_nanf("");  // unreachable; makes a broken replay visible
+      // (unreachable: a broken replay is visible; dist is still what it began with)
+      if (go) vimp = __builtin_nanf("");
     };
     if (OBS != AEB_OBS_NONE && L.pend)
       replay(L.pend, OBS == AEB_OBS_STATIONARY && !ctx.impact_exit ? SAV_PASS : SAV_END, false);
@@ -1691,7 +1692,7 @@ __global__ __launch_bounds__(256) void k_roll_fp64x2(const Job* __restrict__ job
       L[q].collided = L[q].pend = L[q].clamped = false;
       L[q].free_lane = J[q].alim < c[q].a_cmd - 1e-6;
       L[q].limited = J[q].alim > c[q].a_cmd + 1e-9;
-      dist[q] = 0.0;
+      dist[q] = __builtin_nan("");  // until its end is found
       margin[q] = J[q].gap;
       vimp[q] = 0.0f;
       end[q] = steps[q] = 0;
@@ -2123,8 +2124,9 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__
     const int impact_exit = ctx.impact_exit;
     bool boundary = false;
     int end = 0, steps = 0;
-    double dist = 0.0;
-    float vimp = 0.0f;
+    // (until the lane's end, or its impact, is found: a broken replay is visible)
+    double dist = __builtin_nan("");
+    float vimp = __builtin_nanf("");
     int k = 0, wl = -1;
     while (L.active) {
       // the step index is the same in every lane: keep it (and the branches on it) scalar
@@ -2273,7 +2275,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__
           ++kr;
           if (kr % FLUSH == 0) flush32(r, split);
           const float v = speed32<true>(r);
-          if (seek && ((r.X.hi - r.X.lo) + r.p > c.gapf || (!to_stop && kr == se))) {
+          if (seek && (r.X.hi - r.X.lo) + r.p > c.gapf) {
             passed = true;
             seek = false;
             vimp = v;
@@ -2287,7 +2289,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__
             }
             if (!to_stop) go = false;
           }
-          if (to_stop && go && (v <= 0.0f || kr == se)) {
+          if (to_stop && go && v <= 0.0f) {
             end = AEB_END_STOP;
             steps = kr;
             dist = r.X.value(r.p);
@@ -2579,7 +2581,7 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c_lead(const Job* __restr
     L.tame = ballot(al >= 0.0f && J.dmax + al < 100.0);
     bool boundary = false, collided = false;
     int end = 0, steps = 0;
-    double dist = 0.0;
+    double dist = __builtin_nan("");  // until the lane's end is found
     float vimp = 0.0f;
     float gm_end = L.l.gmin;  // running minimum of the clearance when the lane ended
     int k = 0, wl = -1;
@@ -2751,7 +2753,6 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c_lead(const Job* __restr
           }
         }
       }
-      if (go) vimp = __builtin_nanf("");  // unreachable; makes a broken replay visible
     }
     if (!collided) boundary = static_cast<double>(gm_end) < band;
     if (ctx.lanes) count_lanes(ctx.lanes, k, 64);

@@ -102,3 +102,20 @@ def test_stiff_actuator(exe, tmp_path, kernel, obstacle):
     r = subprocess.run([exe, kernel, *map(str, files)], capture_output=True, text=True,
                        timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("obstacle", ["none", "stationary"])
+def test_broken_replay_is_visible(exe, tmp_path, obstacle):
+    """Where a block's replay does not find the stop that the block showed (forced
+    by job records with a wrong bound, under which the steady forms of stiff
+    actuators run), the sample's distance is no number: it is not left without an
+    end, nor given another block's."""
+    from paper_2604_27193_amd import binding
+    path = tmp_path / "diverging"
+    path.write_bytes(b"".join(bytes(binding.scenario(
+        W.single(64, seed=5, scenario_id=j, horizon=0.6, v0=("uniform", v, 6.0 * v),
+                 mu=("uniform", 0.3, 1.0), gap=("uniform", 0.5, 20.0),
+                 grade=("normal", 0.0, 0.1), tau=("uniform", 4e-4, 9e-4),
+                 **OBSTACLES[obstacle]))) for j, v in enumerate((0.5, 1.0, 2.0, 5.0))))
+    r = subprocess.run([exe, "fp32c!", str(path)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
