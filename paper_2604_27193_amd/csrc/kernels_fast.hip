@@ -2920,20 +2920,68 @@ void go64_act(const Shape& sh, const Bufs& b, int64_t n, const Ctx& ctx, const d
                      sh.persistent, act);
 }
 
+// The middle of a distribution, and its share above x (truncation left out).
+double middle(const aeb_dist& d) {
+  if (d.kind == AEB_DIST_UNIFORM) return 0.5 * (d.p0 + d.p1);
+  if (d.kind == AEB_DIST_TRUNC_NORMAL) return std::fmin(std::fmax(d.p0, d.lo), d.hi);
+  return d.p0;
+}
+double share_above(const aeb_dist& d, double x) {
+  if (d.kind == AEB_DIST_CONST || !(d.p1 > (d.kind == AEB_DIST_UNIFORM ? d.p0 : 0.0)))
+    return d.p0 > x ? 1.0 : 0.0;
+  if (d.kind == AEB_DIST_UNIFORM) return std::fmin(std::fmax((d.p1 - x) / (d.p1 - d.p0), 0.0), 1.0);
+  return 0.5 * std::erfc((x - d.p0) / (d.p1 * std::sqrt(2.0)));
+}
+
+// Whether the actuator table gains more than its fill takes, for a scenario with
+// a CONST time constant.  The fill is a serial chain, 65 ns a step, of which the
+// first 75 us run beside the prep, to the last braking step or until the actuator
+// stands still, which at a step of z time constants takes ln(2^53 z) / z steps.
+// The table saves a wavefront's actuator for as long as it is live: to the
+// stop, or about four time constants where friction limits the brake.  A SIMD with
+// w wavefronts saves 25 w + 16 ns a step.  The stop is reckoned at the middles of
+// the distributions.  Rollout calls of the paper's preset, plain form and table, ms:
+// 131,072 samples, tau 0.15 s 1.36 and 1.27, tau 0.5 s 1.45 and 1.73, tau 1 s and a
+// horizon of 30 s 1.54 and 2.96; 350,000, tau 0.5 s 3.04 and 2.78, 30 s 3.05 and
+// 3.09, tau 2.5 s, 60 s 4.16 and 6.77; 1,048,576, tau 0.15 s 7.61 and 5.70, tau 1 s,
+// 30 s 9.16 and 8.72, tau 2.5 s, 60 s 11.4 and 12.1.  Friction about N(0.7, 0.1), which
+// limits half the samples: 100,000 1.16 and 1.27, 200,000 1.78 and 1.66.
+bool act_pays(const aeb_scenario& s, int64_t n) {
+  auto drawn = [&](const aeb_dist& d, int slot) -> const aeb_dist& {
+    return (s.is_mask >> slot) & 1 ? s.proposal[slot] : d;
+  };
+  const aeb_dist& mu = drawn(s.mu, AEB_SLOT_MU);
+  const double tau = s.tau.p0, z = s.dt / tau;
+  const double nmax = static_cast<double>(horizon_steps(s)), nd = static_cast<double>(dead_steps(s));
+  const double fill = std::fmin(nmax - nd, std::fmax(36.74 + std::log(z), 1.0) / z);
+  const double v = middle(drawn(s.v0, AEB_SLOT_V0)), grade = middle(drawn(s.grade, AEB_SLOT_GRADE));
+  const Consts k = derive(s, middle(mu), middle(drawn(s.mass, AEB_SLOT_MASS)), std::sin(grade),
+                          std::cos(grade), middle(drawn(s.cda, AEB_SLOT_CDA)),
+                          middle(drawn(s.crr, AEB_SLOT_CRR)));
+  const double slow = -std::fmax(s.a_cmd, k.alim) + k.c + k.kd * v * v / 3.0;
+  const double stop = slow > 0.0 ? v / slow + tau : s.horizon;
+  // the friction coefficient at which the limit is the command
+  const double amag = -s.a_cmd, reach = s.g - amag * s.h_cog / s.wheelbase;
+  const double free = amag <= 0.0 ? 1.0 : reach > 0.0 ? share_above(mu, amag / reach) : 0.0;
+  const double live = free * stop + (1.0 - free) * std::fmin(stop, 4.0 * tau);
+  const double steps = std::fmin(nmax - nd, live / s.dt);
+  const double w = std::fmax(2.0, static_cast<double>(n) / 65536.0);
+  return 65.0 * fill - 75000.0 < (25.0 * w + 16.0) * steps;
+}
+
 // Bytes of the actuator table (ActTab) of a launch of n samples, 0 where it is
 // not used.  One actuator for all samples: RK4 with a CONST time constant (host
 // columns may hold any), no perception, no controller.  From ACT_MIN samples:
 // below, a SIMD has a wavefront or two, whose speed is a serial chain that the
-// actuator's operations only accompany, and the table takes 0.25 ms to fill
-// (preset of the paper, rollout with and without it: 65,536 samples 1.25 and
-// 1.02 ms, 100,000 1.29 and 1.36, 350,000 2.30 and 2.78, 1,048,576 5.8 and
-// 7.7).  The table takes the space
-// of the command steps and the fix-up list, which such a launch leaves unused
-// (8 bytes a sample); a horizon that needs more keeps the plain form.
+// actuator's operations only accompany (preset of the paper, rollout with and
+// without it: 65,536 samples 1.25 and 1.02 ms, 100,000 1.29 and 1.36, 350,000
+// 2.30 and 2.78, 1,048,576 5.8 and 7.7), and where it pays (act_pays).  The table
+// takes the space of the command steps and the fix-up list, which such a launch
+// leaves unused (8 bytes a sample); a horizon that needs more keeps the plain form.
 constexpr int64_t ACT_MIN = 98304;
 size_t act_bytes(const aeb_scenario& s, int64_t n) {
   if (s.integrator != AEB_RK4 || s.tau.kind != AEB_DIST_CONST || perception_on(s) ||
-      control_on(s) || n < ACT_MIN)
+      control_on(s) || n < ACT_MIN || !act_pays(s, n))
     return 0;
   const size_t steps = static_cast<size_t>(horizon_steps(s));
   const size_t room = 8 * static_cast<size_t>(n);

@@ -119,3 +119,45 @@ def test_broken_replay_is_visible(exe, tmp_path, obstacle):
                  **OBSTACLES[obstacle]))) for j, v in enumerate((0.5, 1.0, 2.0, 5.0))))
     r = subprocess.run([exe, "fp32c!", str(path)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+# (samples, time constant, horizon, step, overrides): calls measured at least 2 %
+# faster on the actuator table, and at least 2 % slower
+MU = {m: {"mu": ("normal", m, 0.1)} for m in (0.6, 0.7)}
+SLOW, HARD = {"v0": ("normal", 10.0, 2.0)}, {"a_cmd": -8.0}
+RARE = {"proposal": {"v0": ("normal", 36.0, 2.0), "mu": ("normal", 0.55, 0.1)}}
+TABLE = [(98304, 0.05, 10, 1e-3, {}), (98304, 0.15, 10, 1e-3, {}), (131072, 0.15, 10, 1e-3, {}),
+         (131072, 0.15, 10, 5e-4, {}), (200000, 0.15, 10, 1e-3, {}),
+         (200000, 0.15, 10, 2e-3, {}), (200000, 2.5, 10, 1e-3, {}), (350000, 0.15, 10, 1e-3, {}),
+         (350000, 0.3, 10, 1e-3, {}), (350000, 0.5, 10, 1e-3, {}), (350000, 2.5, 10, 1e-3, {}),
+         (1048576, 0.15, 10, 1e-3, {}), (1048576, 0.5, 30, 1e-3, {}),
+         (1048576, 0.5, 30, 5e-4, {}), (1048576, 1.0, 30, 1e-3, {}),
+         (1048576, 2.5, 10, 1e-3, {}), (200000, 0.15, 10, 1e-3, MU[0.7]),
+         (350000, 0.15, 10, 1e-3, MU[0.7]), (1048576, 0.15, 10, 1e-3, MU[0.6]),
+         (350000, 1.0, 10, 1e-3, MU[0.6]), (1048576, 1.0, 10, 1e-3, MU[0.6]),
+         (1048576, 0.15, 10, 1e-3, RARE), (350000, 0.15, 10, 1e-3, SLOW),
+         (1048576, 0.15, 10, 1e-3, SLOW), (1048576, 0.15, 10, 1e-3, HARD)]
+PLAIN = [(98304, 0.3, 10, 1e-3, {}), (98304, 0.5, 10, 1e-3, {}), (98304, 2.5, 10, 1e-3, {}),
+         (131072, 0.3, 10, 1e-3, {}), (131072, 0.5, 10, 1e-3, {}), (131072, 0.5, 30, 1e-3, {}),
+         (131072, 1.0, 30, 1e-3, {}), (131072, 2.5, 10, 1e-3, {}), (200000, 0.5, 30, 1e-3, {}),
+         (200000, 1.0, 30, 1e-3, {}), (350000, 0.5, 30, 5e-4, {}), (350000, 1.0, 30, 1e-3, {}),
+         (350000, 2.5, 60, 1e-3, {}), (1048576, 2.5, 60, 1e-3, {}),
+         (100000, 0.15, 10, 1e-3, MU[0.6]), (100000, 0.15, 10, 1e-3, MU[0.7]),
+         (200000, 0.15, 10, 1e-3, MU[0.6]), (100000, 1.0, 10, 1e-3, MU[0.6]),
+         (200000, 1.0, 10, 1e-3, MU[0.6]), (100000, 0.15, 10, 1e-3, RARE),
+         (100000, 0.15, 10, 1e-3, SLOW), (200000, 0.15, 10, 1e-3, SLOW),
+         (100000, 0.15, 10, 1e-3, HARD), (200000, 0.15, 10, 1e-3, HARD),
+         (350000, 0.15, 10, 1e-3, HARD)]
+
+
+def test_actuator_table_only_where_it_pays(exe, tmp_path):
+    from paper_2604_27193_amd import binding
+    path = tmp_path / "scenarios"
+    path.write_bytes(b"".join(bytes(binding.scenario(W.paper_preset(
+        n, tau=("const", tau), horizon=float(h), dt=dt, **over)))
+        for n, tau, h, dt, over in TABLE + PLAIN))
+    r = subprocess.run([exe, "act", str(path)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stderr
+    got = [int(x) for x in r.stdout.split()]
+    want = [1] * len(TABLE) + [0] * len(PLAIN)
+    assert got == want, [c for c, g, w in zip(TABLE + PLAIN, got, want) if g != w]

@@ -136,12 +136,17 @@ bool launch(const std::vector<aeb_scenario>& s, std::vector<Out>& o, Kernel kern
                                        : launch<BATCH, AEB_OBS_STATIONARY, AEB_EULER>(s, o, kern);
 }
 
-bool check(const char* path, Kernel kern) {
+std::vector<aeb_scenario> load(const char* path) {
   std::vector<aeb_scenario> scns;
   aeb_scenario s;
   std::FILE* f = std::fopen(path, "rb");
   while (f && std::fread(&s, sizeof(s), 1, f) == 1) scns.push_back(s);
   if (f) std::fclose(f);
+  return scns;
+}
+
+bool check(const char* path, Kernel kern) {
+  const std::vector<aeb_scenario> scns = load(path);
   if (scns.empty()) return false;
   std::vector<Out> all;
   for (const aeb_scenario& x : scns) all.emplace_back(x.n_samples);
@@ -175,6 +180,12 @@ bool check(const char* path, Kernel kern) {
 int main(int argc, char** argv) {
   if (argc < 3) return 2;
   std::string k = argv[1];
+  if (k == "act") {
+    for (int a = 2; a < argc; ++a)
+      for (const aeb_scenario& s : load(argv[a]))
+        std::printf("%d\n", act_bytes(s, static_cast<int64_t>(s.n_samples)) > 0);
+    return 0;
+  }
   g_wrong_bound = k.back() == '!';
   if (g_wrong_bound) k.pop_back();
   const Kernel kern = k == "fp64" ? FP64 : k == "fp64x2" ? FP64X2 : FP32C;
