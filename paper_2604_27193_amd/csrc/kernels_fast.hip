@@ -530,10 +530,46 @@ __global__ __launch_bounds__(SORT1_T) void k_sort1(const uint32_t* keys, int64_t
   }
   for (int j = t; j < NB; j += SORT1_T) cnt[j] = 0;
   __syncthreads();
+  // Adds of one wavefront to one counter run one after the other.  Where a launch
+  // has few keys (parameters that do not vary, a horizon that ends every sample)
+  // that set the sort's time: lanes that share a key then add once (rollout of
+  // 32,768 samples of one key 139 -> 120 us, the separate kernels 128; of two keys
+  // 110 -> 103, 106).  Taken where two keys cover half of a wavefront's first
+  // samples: more keys are counted faster one by one.
+  unsigned long long left = __ballot(t < n);
+  const unsigned long long first = left;
+  for (int q = 0; q < 2 && left; ++q)
+    left &= ~__ballot(key[0] == __shfl(key[0], __ffsll(static_cast<long long>(left)) - 1));
+  const bool few = 2 * __popcll(left) <= __popcll(first);
+  if (few) {
+    const unsigned long long below = (1ull << (t & 63)) - 1ull;
 #pragma unroll
-  for (int r = 0; r < SPT; ++r) {
-    const int64_t i = static_cast<int64_t>(r) * SORT1_T + t;
-    rank[r] = i < n ? atomicAdd(&cnt[key[r]], 1u) : 0u;
+    for (int r = 0; r < SPT; ++r) {
+      bool mine = static_cast<int64_t>(r) * SORT1_T + t < n;
+      rank[r] = 0u;
+      for (int q = 0; q < 2; ++q) {
+        const unsigned long long who = __ballot(mine);
+        if (who == 0) break;
+        const int from = __ffsll(static_cast<long long>(who)) - 1;
+        const unsigned long long same =
+            __ballot(mine && key[r] == static_cast<uint32_t>(__shfl(key[r], from)));
+        uint32_t base = 0;
+        if ((t & 63) == from)
+          base = atomicAdd(&cnt[key[r]], static_cast<uint32_t>(__popcll(same)));
+        base = __shfl(base, from);
+        if (same >> (t & 63) & 1) {
+          rank[r] = base + static_cast<uint32_t>(__popcll(same & below));
+          mine = false;
+        }
+      }
+      if (mine) rank[r] = atomicAdd(&cnt[key[r]], 1u);
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < SPT; ++r) {
+      const int64_t i = static_cast<int64_t>(r) * SORT1_T + t;
+      rank[r] = i < n ? atomicAdd(&cnt[key[r]], 1u) : 0u;
+    }
   }
   __syncthreads();
   // exclusive scan of the counts, PER consecutive bins per thread
