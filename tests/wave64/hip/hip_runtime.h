@@ -126,10 +126,18 @@ inline int __builtin_amdgcn_update_dpp(int old, int src, int ctrl, int rows, int
   if (ctrl <= 0x110 || ctrl > 0x11f) std::abort();
   return l % 16 >= ctrl - 0x110 ? static_cast<int>(o[l - (ctrl - 0x110)]) : old;
 }
+// (named in kernels that synchronise a workgroup, which are not run here)
 template <class T>
 T __shfl_up(T, int) {
   std::abort();
 }
+template <class T>
+T __shfl(T, int) {
+  std::abort();
+}
+inline unsigned long long __ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+inline int __popcll(unsigned long long x) { return __builtin_popcountll(x); }
+inline int __ffsll(long long x) { return __builtin_ffsll(x); }
 inline void __syncthreads() { std::abort(); }
 template <class T, class U>
 T atomicAdd(T* p, U v) {
