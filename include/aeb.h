@@ -444,7 +444,8 @@ int aeb_reduce(const aeb_outputs* out, const aeb_reduce_req* req, aeb_stats* hos
  * steps per unchecked block (16, 32 or 64; AEB_FP64 also 128), the workgroup
  * size (64, 128, 256), waves_per_simd (0: one workgroup per `block` (or
  * 2 x `block`) samples in one pass; 1..32: a persistent grid of that many
- * wavefronts per SIMD claiming chunks of 64 (or 128) samples), and
+ * wavefronts per SIMD claiming chunks of 64 (or 128) samples; of the built-in
+ * shape fewer, at least 2, where a launch has fewer chunks), and
  * samples_per_thread (1; or 2 for AEB_FP64 explicit Euler in the fused form
  * without a lead vehicle or controller: each lane integrates two sorted
  * samples, interleaving their steps; other scenarios of such an entry run

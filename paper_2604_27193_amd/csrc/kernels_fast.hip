@@ -2845,9 +2845,10 @@ struct Shape {
 // are left over, go to the SIMDs that are done first.  FP64, kernel with 4 and
 // with 3: 200,000 samples 0.258 and 0.237 ms, with a lead 0.432 and 0.346, RK4
 // 1.50 and 1.29; 160,000 with 4 and with 2: 0.209 and 0.198.  Not under the
-// controller (spread: false), whose wavefronts wait on their draws: 200,000
-// samples 0.485 and 0.523.
-Shape shape(const TuneCfg& t, int64_t n, int spt = 1, bool spread = true) {
+// controller, whose wavefronts wait on their draws: 200,000 samples 0.485 and
+// 0.523; and only the built-in shapes (spread): one that was set or tuned starts
+// the wavefronts that it says.
+Shape shape(const TuneCfg& t, int64_t n, int spt, bool spread) {
   static int cus = 0;
   if (cus == 0) {
     int dev = 0;
@@ -3084,8 +3085,10 @@ int integrate(const aeb_scenario& s0, int precision, const Bufs& b, int64_t n, c
               const ParamSrc* src, hipStream_t st, const double* act = nullptr) {
   const int obs = s0.obstacle;
   Ctx ctx = ctx_in;
-  const TuneCfg t = tune_get(precision == AEB_FP64 ? AEB_FP64 : AEB_FP32C, obs);
-  const Shape sh = shape(t, n, 1, BATCH || !control_on(s0));
+  const int form = precision == AEB_FP64 ? AEB_FP64 : AEB_FP32C;
+  const TuneCfg t = tune_get(form, obs);
+  const bool builtin = tune_is_builtin(form, obs, t);
+  const Shape sh = shape(t, n, 1, builtin && (BATCH || !control_on(s0)));
   if (!BATCH && control_on(s0)) {
     // the controller decides every ctl_period and blocks stay within a
     // decision period: the top level is a block size that divides the period
@@ -3147,7 +3150,7 @@ int integrate(const aeb_scenario& s0, int precision, const Bufs& b, int64_t n, c
   }
   if (precision == AEB_FP64 && t.spt == 2 && obs != AEB_OBS_LEAD) {
     // two samples per lane (the tuned FP64 shape)
-    const Shape sh2 = shape(t, n, 2);
+    const Shape sh2 = shape(t, n, 2, builtin);
     arm_lanes(ctx, st);
     timing_begin(st);
     if (obs == AEB_OBS_STATIONARY)

@@ -24,13 +24,9 @@ namespace {
 std::mutex g_mu;
 std::once_flag g_env_once;
 // [precision 0 FP64, 1 FP32C][obstacle none, stationary, lead]
-// defaults measured on MI355X (1,048,576-sample workloads, launch shapes
-// timed in one process, interleaved): FP64 256 threads and 4 persistent
-// wavefronts per SIMD, 128-step blocks with an obstacle and 64-step blocks
-// without; FP32C 64-step blocks, 256 threads, one pass
 TuneCfg g_tab[2][3] = {
-    {{64, 256, 4, 1}, {128, 256, 4, 1}, {128, 256, 4, 1}},
-    {{64, 256, 0, 1}, {64, 256, 0, 1}, {64, 256, 0, 1}},
+    {TUNE_BUILTIN[0][0], TUNE_BUILTIN[0][1], TUNE_BUILTIN[0][2]},
+    {TUNE_BUILTIN[1][0], TUNE_BUILTIN[1][1], TUNE_BUILTIN[1][2]},
 };
 std::vector<TuneResult> g_res[2][3];  // the last sweep's candidates
 

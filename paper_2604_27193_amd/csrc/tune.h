@@ -16,6 +16,24 @@ struct TuneCfg {
                        // vehicle or controller: each lane integrates two sorted samples)
 };
 
+// The built-in shapes, [precision 0 FP64, 1 FP32C][obstacle none, stationary,
+// lead], measured on MI355X (1,048,576-sample workloads, launch shapes timed in
+// one process, interleaved): FP64 256 threads and 4 persistent wavefronts per
+// SIMD, 128-step blocks with an obstacle and 64-step blocks without; FP32C
+// 64-step blocks, 256 threads, one pass
+constexpr TuneCfg TUNE_BUILTIN[2][3] = {
+    {{64, 256, 4, 1}, {128, 256, 4, 1}, {128, 256, 4, 1}},
+    {{64, 256, 0, 1}, {64, 256, 0, 1}, {64, 256, 0, 1}},
+};
+
+// Whether t is the built-in shape: only that one may start fewer wavefronts
+// than it says (shape() of the integration kernels); one that was set, tuned or
+// loaded runs as it is.
+inline bool tune_is_builtin(int precision, int obstacle, const TuneCfg& t) {
+  const TuneCfg& b = TUNE_BUILTIN[precision == 0 ? 0 : 1][obstacle < 0 || obstacle > 2 ? 0 : obstacle];
+  return t.k == b.k && t.block == b.block && t.waves_per_simd == b.waves_per_simd && t.spt == b.spt;
+}
+
 // One timed candidate of the last autotuner sweep.
 struct TuneResult {
   TuneCfg t;

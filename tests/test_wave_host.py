@@ -161,3 +161,20 @@ def test_actuator_table_only_where_it_pays(exe, tmp_path):
     got = [int(x) for x in r.stdout.split()]
     want = [1] * len(TABLE) + [0] * len(PLAIN)
     assert got == want, [c for c, g, w in zip(TABLE + PLAIN, got, want) if g != w]
+
+
+# precision, obstacle, k, block, waves per SIMD, samples per thread, samples ->
+# wavefronts started on 1,024 SIMDs
+SHAPES = [((0, 1, 128, 256, 4, 1, 1 << 20), 4096), ((0, 1, 128, 256, 4, 1, 200_000), 3072),
+          ((0, 1, 128, 256, 4, 1, 100_000), 1564), ((0, 0, 64, 256, 4, 1, 160_000), 2048),
+          # set or tuned: what they say, as far as there are chunks
+          ((0, 1, 128, 256, 8, 1, 1 << 20), 8192), ((0, 1, 128, 256, 8, 1, 200_000), 3128),
+          ((0, 1, 64, 256, 4, 1, 200_000), 3128), ((0, 2, 128, 64, 3, 1, 160_000), 2500),
+          ((0, 1, 128, 256, 1, 1, 200_000), 1024), ((0, 1, 128, 256, 3, 2, 300_000), 2344),
+          ((1, 1, 64, 256, 4, 1, 200_000), 3128), ((1, 1, 64, 256, 0, 1, 200_000), 3128)]
+
+
+@pytest.mark.parametrize("args,waves", SHAPES)
+def test_launch_shape(exe, args, waves):
+    r = subprocess.run([exe, "shape", *map(str, args)], capture_output=True, text=True)
+    assert r.returncode == 0 and int(r.stdout) == waves

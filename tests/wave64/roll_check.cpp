@@ -180,6 +180,13 @@ bool check(const char* path, Kernel kern) {
 int main(int argc, char** argv) {
   if (argc < 3) return 2;
   std::string k = argv[1];
+  if (k == "shape" && argc == 9) {
+    const TuneCfg t{std::atoi(argv[4]), std::atoi(argv[5]), std::atoi(argv[6]), std::atoi(argv[7])};
+    const Shape sh = shape(t, std::atoll(argv[8]), t.spt,
+                           tune_is_builtin(std::atoi(argv[2]), std::atoi(argv[3]), t));
+    std::printf("%u\n", sh.grid * sh.block / 64);
+    return 0;
+  }
   if (k == "act") {
     for (int a = 2; a < argc; ++a)
       for (const aeb_scenario& s : load(argv[a]))
