@@ -27,8 +27,9 @@
  *   - All functions act on the HIP device that is current on the calling thread.
  *   - The library keeps a per-device pool of scratch blocks for sorting and
  *     reduction partials; it grows on demand (hipMalloc, and with each block
- *     pinned memory for one aeb_stats) and lives until process exit.  A call that needs scratch (aeb_rollout, aeb_reduce,
- *     aeb_batch_rollout, aeb_batch_reduce, aeb_autotune) holds its blocks
+ *     pinned memory for one aeb_stats) and lives until process exit.  A call
+ *     that needs scratch (aeb_rollout, aeb_reduce, aeb_batch_rollout,
+ *     aeb_batch_reduce, aeb_autotune) holds its blocks
  *     while it enqueues work and then fences them with an event on its
  *     stream; another call reuses a block only once that work is done (or
  *     after its stream waits for the event on the device), and a block is

@@ -610,7 +610,7 @@ __global__ __launch_bounds__(SORT1_T) void k_sort1(const uint32_t* keys, int64_t
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < SPT; ++r) {
-        if (rank[r] - lo < STAGE && rank[r] != ~0u)
+      if (rank[r] - lo < STAGE && rank[r] != ~0u)
         stage[rank[r] - lo] = static_cast<uint16_t>(r * SORT1_T + t);
     }
     __syncthreads();
@@ -1212,11 +1212,12 @@ HOT int run_steady(Wave64& L, Saves64<OBS>& S, const Job& J, double al, double d
 
 template <int OBS, int K, bool BATCH, int INTEG = AEB_EULER, bool CTL = false, bool TAB = false>
 __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ jobs,
-                                                   const LeadJob* __restrict__ leads,
-                                                   const uint32_t* __restrict__ perm, int64_t n,
-                                                   Ctx ctx, unsigned long long* counter,
-                                                   int persistent,
-                                                   const double* __restrict__ act) {
+                                                        const LeadJob* __restrict__ leads,
+                                                        const uint32_t* __restrict__ perm,
+                                                        int64_t n, Ctx ctx,
+                                                        unsigned long long* counter,
+                                                        int persistent,
+                                                        const double* __restrict__ act) {
   ActTab at{nullptr, 0, 0};
   if (TAB) at = ActTab{act + ACT_HDR, *reinterpret_cast<const int*>(act), ctx.nd};
   if (ctx.hdr) n = ctx.hdr->total;  // a recorded mix: its size from the device header
@@ -1577,10 +1578,11 @@ __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp64(const Job* __restrict__ 
 // stationary one, no controller): lane l of a wavefront integrates the
 // sorted positions base + l and base + 64 + l of a 128-sample chunk, so a
 // wavefront's block bookkeeping, ladder and replay serve twice the samples
-// and every block interleaves two independent dependency chains.  The forms,
-// ladder, block limits and crossing replay are those of k_roll_fp64, taken
-// over both samples of every lane; each sample's steps are the canonical
-// step's, bit for bit.
+// and every block interleaves two independent dependency chains.  The forms and
+// block limits are those of k_roll_fp64, taken over both samples of every lane.
+// The ladder leaves a level as soon as a sample could stop inside its block, so
+// stops fall on checked steps and only crossings are replayed.  Each sample's
+// steps are the canonical step's, bit for bit.
 // ---------------------------------------------------------------------------
 // state and flags of one of a lane's samples
 struct Lane64x2 {
@@ -2061,9 +2063,9 @@ HOT bool long_block32(const Wave32& L, float thr, lanes_t fall) {
 // K-step pieces of a run between its tests: two, unrolled, for a wavefront with
 // split speeds in a batched launch, whose wavefronts are long and many, so that
 // the tests' share is worth a longer replay of the block with the crossing or the
-// stop (1,000 uneven scenarios, most of their steps split: kernel 32.4 -> 30.4
-// ms); one elsewhere (1,048,576 samples of one scenario 0.575 ms, 0.59 with two;
-// 200,000 0.157 and 0.165).
+// stop (1,000 uneven scenarios, most of their steps split: kernel 30.1 ms with
+// one, 29.6 with two); one elsewhere (1,048,576 samples of one scenario 0.551 ms,
+// 0.565 with two; 200,000 0.150 and 0.159).
 template <int K, bool BATCH>
 constexpr int run_pieces() { return BATCH && K == FLUSH ? 2 : 1; }
 
@@ -2103,10 +2105,11 @@ HOT int run_steady32(Wave32& L, Saves32<OBS>& S, const L32& c, float tk, bool sp
 
 template <int OBS, int K, bool BATCH>
 __global__ __launch_bounds__(ROLL_MAX) void k_roll_fp32c(const Job* __restrict__ jobs,
-                                                    const uint32_t* __restrict__ perm, int64_t n,
-                                                    Ctx ctx, double band_abs, double band_rel,
-                                                    uint32_t* fix, unsigned long long* counter,
-                                                    int persistent) {
+                                                         const uint32_t* __restrict__ perm,
+                                                         int64_t n, Ctx ctx, double band_abs,
+                                                         double band_rel, uint32_t* fix,
+                                                         unsigned long long* counter,
+                                                         int persistent) {
   if (ctx.hdr) n = ctx.hdr->total;  // a recorded mix: its size from the device header
   // the block ladder of the FP64 kernel, blocks starting on multiples of their length
   constexpr int KS = 4;
@@ -2989,9 +2992,11 @@ bool act_pays(const aeb_scenario& s, int64_t n) {
   };
   const aeb_dist& mu = drawn(s.mu, AEB_SLOT_MU);
   const double tau = s.tau.p0, z = s.dt / tau;
-  const double nmax = static_cast<double>(horizon_steps(s)), nd = static_cast<double>(dead_steps(s));
+  const double nmax = static_cast<double>(horizon_steps(s));
+  const double nd = static_cast<double>(dead_steps(s));
   const double fill = std::fmin(nmax - nd, std::fmax(36.74 + std::log(z), 1.0) / z);
-  const double v = middle(drawn(s.v0, AEB_SLOT_V0)), grade = middle(drawn(s.grade, AEB_SLOT_GRADE));
+  const double v = middle(drawn(s.v0, AEB_SLOT_V0));
+  const double grade = middle(drawn(s.grade, AEB_SLOT_GRADE));
   const Consts k = derive(s, middle(mu), middle(drawn(s.mass, AEB_SLOT_MASS)), std::sin(grade),
                           std::cos(grade), middle(drawn(s.cda, AEB_SLOT_CDA)),
                           middle(drawn(s.crr, AEB_SLOT_CRR)));

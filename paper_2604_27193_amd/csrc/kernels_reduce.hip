@@ -1105,8 +1105,8 @@ __global__ __launch_bounds__(EB) void k_small_collect(RSegs S, RReq rq) {
 // ---- fallback: most-significant-digit radix select, 8 passes of 8 bits ----
 // The sets whose selection asks for it, FB_SETS of them per launch sequence
 // (by value in the kernel arguments): every kernel covers all of them, so a
-// batch with many such sets costs one sequence of 18 short launches and not
-// one per set.  26 sets of 100,000 samples (a sweep's scenarios in which most
+// batch with many such sets costs one sequence of 17 short launches per FB_SETS
+// and not one per set, and then two small copies per set.  26 sets of 100,000 samples (a sweep's scenarios in which most
 // samples collide share one margin bin): 0.35 ms against 20 ms one set after the
 // other with two wavefronts per SIMD at work on one of 36.
 constexpr int FB_SETS = FALLBACK_SETS;
